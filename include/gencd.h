@@ -142,7 +142,11 @@ typedef struct {
   int32_t piece;         /* nonzeros per piece of a long column (multiple of 64,
                             64..2^22); 0 = library default */
   int32_t group;         /* lanes per short column (4, 8, 16 or 32); columns of
-                            at most 4 * group nonzeros are short; 0 = default */
+                            at most 4 * group nonzeros are short; 0 = default.
+                            With piece, group and residual all 0 a small problem
+                            may run whole epochs in one launch instead of one
+                            launch pair per iteration (same iterates up to FP32
+                            rounding); setting one keeps the pairs */
   int32_t improve_steps; /* "Improve delta_j" (Algorithm 3, section 4.1): up to this
                             many further quadratic-approximation steps on each
                             accepted proposal's 1-D objective, from the state at

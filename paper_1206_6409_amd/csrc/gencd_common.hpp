@@ -27,15 +27,12 @@ constexpr int kUnroll = 4;   // CSC entries a lane keeps in flight per round
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float dloss_f32(int loss, float y, float t) {
   if (loss == GENCD_SQUARED) return t - y;
-  float m = y * t;  // -y * sigma(-m), evaluated without overflow
-  float s;
-  if (m >= 0.0f) {
-    float e = expf(-m);
-    s = e / (1.0f + e);
-  } else {
-    s = 1.0f / (1.0f + expf(m));
-  }
-  return -y * s;
+  // -y * sigma(-m) without overflow: e = exp(-|m|), the numerator selected by
+  // the sign (lanes of a wave hold both signs, so a branch would run both
+  // sides; the values are those of the branches e / (1 + e), 1 / (1 + e))
+  const float m = y * t;
+  const float e = expf(-fabsf(m));
+  return -y * ((m >= 0.0f ? e : 1.0f) / (1.0f + e));
 }
 
 __device__ __forceinline__ double loss_f64(int loss, double y, double t) {
@@ -49,15 +46,9 @@ __device__ __forceinline__ double loss_f64(int loss, double y, double t) {
 
 __device__ __forceinline__ double dloss_f64(int loss, double y, double t) {
   if (loss == GENCD_SQUARED) return t - y;
-  double m = y * t;
-  double s;
-  if (m >= 0.0) {
-    double e = exp(-m);
-    s = e / (1.0 + e);
-  } else {
-    s = 1.0 / (1.0 + exp(m));
-  }
-  return -y * s;
+  const double m = y * t;  // as dloss_f32
+  const double e = exp(-fabs(m));
+  return -y * ((m >= 0.0 ? e : 1.0) / (1.0 + e));
 }
 
 // Proposal from the quadratic upper bound (Algorithm 4: Eq. 7 for the step,
@@ -151,6 +142,25 @@ __device__ __forceinline__ T group_sum(T v) {
 #pragma unroll
   for (int off = G / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   return v;
+}
+
+// Sum over an aligned group of N = 4, 8 or 16 lanes with DPP moves inside
+// a row (xor 1, xor 2, half-row mirror, row mirror): every stage adds the
+// partner's partial to the lane's own, and the partner adds the same two
+// values, so every lane of the group ends with the same bits.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+template <int N>
+__device__ __forceinline__ float row_group_sum(float x) {
+  static_assert(N == 4 || N == 8 || N == 16, "groups inside one DPP row");
+  x += dpp_move<0xB1>(x);   // quad_perm [1, 0, 3, 2]
+  x += dpp_move<0x4E>(x);   // quad_perm [2, 3, 0, 1]
+  if constexpr (N >= 8) x += dpp_move<0x141>(x);   // row_half_mirror
+  if constexpr (N >= 16) x += dpp_move<0x140>(x);  // row_mirror
+  return x;
 }
 
 // Rounding error of a + b (TwoSum, exact in round-to-nearest).
@@ -268,7 +278,7 @@ int radix_sort_pairs(uint32_t *k0, int32_t *v0, uint32_t *k1, int32_t *v1, int64
 // the epochs run so far (1 for the first twenty, at most 64), so a solve
 // that first meets its tolerance at epoch N is checked by about 1.1 N;
 // check_every = -m adapts it to an m-th (checked by about (1 + 1/m) N).
-inline int64_t check_interval(int64_t check_every, int64_t done) {
+__host__ __device__ inline int64_t check_interval(int64_t check_every, int64_t done) {
   if (check_every > 0) return check_every;
   const int64_t m = check_every < 0 ? -check_every : 10;
   const int64_t c = done / m;

@@ -368,14 +368,27 @@ __device__ __forceinline__ Roles roles(int32_t nl_req) {
 __global__ __launch_bounds__(kBlock) void k_col_counts(const int64_t *col_ptr, int64_t k,
                                                         int piece, int short_max,
                                                         int32_t *scnt, int32_t *lcnt,
-                                                        int32_t *live_flag) {
+                                                        int32_t *live_flag,
+                                                        unsigned long long *max_len) {
+  unsigned long long longest = 0;
   for (int64_t j = int64_t(blockIdx.x) * kBlock + threadIdx.x; j < k;
        j += int64_t(gridDim.x) * kBlock) {
     const int64_t m = col_ptr[j + 1] - col_ptr[j];
     scnt[j] = (m > 0 && m <= short_max) ? 1 : 0;
     lcnt[j] = m > short_max ? int32_t((m + piece - 1) / piece) : 0;
     live_flag[j] = m > 0 ? 1 : 0;
+    if ((unsigned long long)m > longest) longest = (unsigned long long)m;
   }
+  // longest column: one atomic per wave at most, and none once a longer
+  // column is known (atomics on one address queue)
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    const unsigned long long o = __shfl_xor(longest, off);
+    longest = o > longest ? o : longest;
+  }
+  if ((threadIdx.x & (kWave - 1)) == 0 &&
+      longest > __hip_atomic_load(max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(max_len, longest);
 }
 
 __global__ __launch_bounds__(kBlock) void k_col_scatter(const int64_t *col_ptr, int64_t k,
@@ -462,7 +475,8 @@ int launch_preprocess(const gencd_csc *X, int loss, int piece, int short_max, co
   const int64_t k = X->k;
   // counts: short -> tmp_cnt, long pieces -> tmp_cnt2, live flags -> col_of_pos (scratch)
   hipLaunchKernelGGL(k_col_counts, dim3(grid_for(k)), dim3(kBlock), 0, s, X->col_ptr, k, piece,
-                     short_max, w.tmp_cnt, w.tmp_cnt2, w.col_of_pos);
+                     short_max, w.tmp_cnt, w.tmp_cnt2, w.col_of_pos,
+                     reinterpret_cast<unsigned long long *>(w.red) + 11);
   int st = scan_exclusive(w.tmp_cnt, w.all_soff, k, w.scan_part, s);
   if (st) return st;
   st = scan_exclusive(w.tmp_cnt2, w.all_loff, k, w.scan_part, s);

@@ -38,6 +38,47 @@ struct IterArgs {
                                  // (replica line b % kChkRep of workgroup b, 16 words each)
 };
 
+// Whole epochs of a small accept-all problem in one workgroup
+// (gencd_solo.hip).
+struct SoloOut {
+  int64_t epoch, next_check;  // epochs run so far, and the next due check
+  double objective, kkt, gap, drift, best;  // the last check; drift: the largest
+  int64_t nnz_w, checked;     // checked: the launch ended on a check
+};
+
+struct SoloArgs {
+  const int64_t *col_ptr;
+  const int32_t *row_idx;
+  const float *val;
+  const float *c;
+  const int32_t *live;
+  float *w, *w_ckpt;
+  float4 *zs;
+  int4 *rec;         // [k_live] column records in index order (build_rec: written first)
+  int4 *desc;        // [k_live] scratch: the epoch order
+  double *z64;       // [n] Xw of the last check
+  SoloOut *out;
+  int64_t k, k_live;
+  int32_t n, S, loss, natural, inner, build_rec;
+  int32_t max_len;   // entries of the longest column
+  float lam, n_f;
+  double lam64, inv_n, kkt_tol, gap_tol, best;
+  uint64_t seed;
+  int64_t e0, max_epochs, next_check, check_every, max_windows;
+};
+
+struct SoloPlan {
+  bool ok, inner;    // inner: the FP64 checks run in the same launch
+  bool one;          // a window fits one wave
+  int G, U;          // lanes per column, entries per lane and batch
+  size_t lds;
+};
+
+// Shape for windows of S columns of a matrix whose longest column has
+// max_len entries (ok = false: the multi-workgroup kernels take it).
+SoloPlan solo_plan(int64_t n, int64_t nnz, int64_t k_live, int64_t max_len, int64_t S);
+int launch_solo(const SoloArgs &a, const SoloPlan &p, hipStream_t s);
+
 int fill_f32(float *p, int64_t m, float v, hipStream_t s);
 int fill_i32(int32_t *p, int64_t m, int32_t v, hipStream_t s);
 int fill_f64(double *p, int64_t m, double v, hipStream_t s);

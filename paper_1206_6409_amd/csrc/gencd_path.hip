@@ -179,25 +179,6 @@ __device__ __forceinline__ float dloss_fast_f32(int loss, float y, float t) {
   return -y * ((m >= 0.0f ? e : 1.0f) * __builtin_amdgcn_rcpf(1.0f + e));
 }
 
-// Sum over an aligned group of N = 4, 8 or 16 lanes with DPP moves inside
-// a row (xor 1, xor 2, half-row mirror, row mirror): every stage adds the
-// partner's partial to the lane's own, and the partner adds the same two
-// values, so every lane of the group ends with the same bits.
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-
-template <int N>
-__device__ __forceinline__ float row_group_sum(float x) {
-  static_assert(N == 4 || N == 8 || N == 16, "groups inside one DPP row");
-  x += dpp_move<0xB1>(x);   // quad_perm [1, 0, 3, 2]
-  x += dpp_move<0x4E>(x);   // quad_perm [2, 3, 0, 1]
-  if constexpr (N >= 8) x += dpp_move<0x141>(x);   // row_half_mirror
-  if constexpr (N >= 16) x += dpp_move<0x140>(x);  // row_mirror
-  return x;
-}
-
 // One column of at most 64 entries (two batches) in LDS for
 // path_improve_wave; the first step's batch loop stages it.
 constexpr int kImproveMax = 64;

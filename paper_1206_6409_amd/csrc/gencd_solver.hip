@@ -228,6 +228,7 @@ int setup(const gencd_csc *X, const float *y, int loss, const gencd_params *p, v
   out->n_short = host[0];
   out->k_live = host[1];
   out->n_lpieces = host[2];
+  out->max_len = int64_t(r.max_len);
   st = launch_curvature(X, loss, out->n_short, out->n_lpieces, w, s);
   if (st) return st;
   if (rho_iters > 0) {
@@ -489,6 +490,10 @@ bool wants_rs(const gencd_params *p, int64_t positions, int64_t nnz, int64_t k_l
   return double(positions) * double(nnz) / double(k_live) >= 4.0 * double(n);
 }
 
+// Windows of one single-workgroup launch (a few to a few tens of
+// milliseconds, so that other streams' work is not held up for long).
+constexpr int64_t kSoloMaxWindows = 16384;
+
 // Expected long pieces in a window of `positions` columns (sizes the grid;
 // the kernels stride over the actual count).
 int64_t long_bound_for(const Setup &su, int64_t positions) {
@@ -648,6 +653,15 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
   };
   GraphHolder graph;
   int64_t graph_S = -1;
+  // Small windows: whole epochs in one workgroup.  A caller who fixed the
+  // multi-workgroup schedule (piece, group, residual form) or asked for
+  // something only those kernels do keeps them; the results are the same.
+  const bool solo_rule =
+      (rule == GENCD_CYCLIC || rule == GENCD_STOCHASTIC || rule == GENCD_SHOTGUN) && !prof &&
+      !fused && !a.exact_accum && p->improve_steps == 0 && p->piece == 0 && p->group == 0 &&
+      p->residual == 0;
+  // a restart with half the window (divergence guard) keeps the choice
+  const bool solo = solo_rule && solo_plan(X->n, X->nnz, k_live, su.max_len, S).ok;
 
   // Enqueue one epoch: selection order (section 2.1), then every iteration
   // of Algorithm 1, then the epoch counter increment.  Every argument is
@@ -728,7 +742,59 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
           if (hipEventCreateWithFlags(&ev, hipEventDisableSystemFence) != hipSuccess) ev = nullptr;
       }
     }
-    if (use_graph) {
+    int64_t ran = 1;       // epochs of this pass of the loop
+    bool checked = false;  // ck already holds the check that ends them
+    if (solo) {
+      const SoloPlan plan = solo_plan(X->n, X->nnz, k_live, su.max_len, S);
+      SoloArgs sa{};
+      sa.col_ptr = X->col_ptr;
+      sa.row_idx = X->row_idx;
+      sa.val = X->val;
+      sa.c = ws.c;
+      sa.live = ws.live;
+      sa.w = w;
+      sa.w_ckpt = ws.w_ckpt;
+      sa.zs = ws.zs;
+      sa.rec = ws.live_rec;  // not read by anything else in such a solve
+      sa.build_rec = e == 0 ? 1 : 0;
+      sa.desc = ws.desc_s;
+      sa.z64 = ws.z64;
+      sa.out = reinterpret_cast<SoloOut *>(ws.rrep);
+      sa.k = X->k;
+      sa.k_live = k_live;
+      sa.n = int32_t(X->n);
+      sa.S = int32_t(S);
+      sa.max_len = int32_t(su.max_len);
+      sa.loss = p->loss;
+      sa.natural = rule == GENCD_CYCLIC ? 1 : 0;
+      sa.inner = plan.inner ? 1 : 0;
+      sa.lam = float(p->lambda);
+      sa.n_f = float(X->n);
+      sa.lam64 = p->lambda;
+      sa.inv_n = 1.0 / double(X->n);
+      sa.kkt_tol = p->kkt_tol;
+      sa.gap_tol = p->gap_tol;
+      sa.best = best;
+      sa.seed = p->seed;
+      sa.e0 = e;
+      sa.max_epochs = p->max_epochs;
+      sa.next_check = next_check;
+      sa.check_every = check_every;
+      sa.max_windows = kSoloMaxWindows;
+      st = launch_solo(sa, plan, s);
+      if (st) return st;
+      SoloOut so{};
+      GENCD_HIP(hipMemcpyAsync(&so, sa.out, sizeof(so), hipMemcpyDeviceToHost, s));
+      GENCD_HIP(hipStreamSynchronize(s));
+      ran = so.epoch - e;
+      if (ran < 1) return GENCD_ERR_HIP;  // cannot happen
+      if (plan.inner) {
+        checked = so.checked != 0;
+        ck = CheckOut{so.objective, so.kkt, so.gap, so.nnz_w, 0, 0, so.drift};
+        next_check = so.next_check;
+        best = so.best;
+      }
+    } else if (use_graph) {
       if (graph_S != S) {
         // capture on a private stream (the caller's may be the legacy
         // default stream, which cannot be captured); replay on the caller's
@@ -763,20 +829,23 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       iters = 0;
       for (int32_t sz : cls_sizes) iters += sz > 0;
     }
-    st_out->iters += iters;
-    if (mode != 2) st_out->coord_updates += k_live;
+    e += ran - 1;
+    st_out->iters += iters * ran;
+    if (mode != 2) st_out->coord_updates += k_live * ran;
     st_out->epochs = e + 1;
     if (!evs.empty()) {
       prof_bytes_pending += 12.0 * double(X->nnz) + 28.0 * double(k_live);
       // accept-all rules: every live column is accepted once per epoch
       if (mode != 2) prof_ubytes_pending += 24.0 * double(X->nnz) + 8.0 * double(k_live);
     }
-    st_out->nnz_visits += X->nnz;
-    if (mode != 2) st_out->nnz_updates += X->nnz;
-    if (e + 1 >= next_check || e + 1 == p->max_epochs) {
-      next_check = e + 1 + check_interval(check_every, e + 1);
-      st = run_check(X, y, p->loss, p->lambda, w, su, true, s, &ck);
-      if (st) return st;
+    st_out->nnz_visits += X->nnz * ran;
+    if (mode != 2) st_out->nnz_updates += X->nnz * ran;
+    if (checked || e + 1 >= next_check || e + 1 == p->max_epochs) {
+      if (!checked) {
+        next_check = e + 1 + check_interval(check_every, e + 1);
+        st = run_check(X, y, p->loss, p->lambda, w, su, true, s, &ck);
+        if (st) return st;
+      }
       if (std::isfinite(ck.drift_rel))
         st_out->z_drift = std::max(st_out->z_drift, ck.drift_rel);
       else

@@ -17,7 +17,7 @@ struct Red {
   unsigned long long gmax_bits;
   double dual_sum;
   unsigned long long pad[2];
-  unsigned long long acc_nnz, acc_cnt, bad, spare;
+  unsigned long long acc_nnz, acc_cnt, bad, max_len;  // max_len: set by the set-up
   unsigned long long pad2[4];
 };
 static_assert(sizeof(Red) == 16 * 8, "reduction block layout");
@@ -27,6 +27,7 @@ struct Setup {
   int piece = kDefaultPiece, group = kDefaultGroup;
   int32_t n_short = 0, n_lpieces = 0;
   int64_t k_live = 0;
+  int64_t max_len = 0;           // entries of the longest column
   std::vector<double> rho_hist;  // spectral-radius estimate after each power iteration
   double rho = 0.0;
   std::vector<double> brho;      // Block Shotgun: rho_b of every preset block
