@@ -163,6 +163,52 @@ __device__ __forceinline__ float row_group_sum(float x) {
   return x;
 }
 
+// One step of a reduction inside a DPP row: the partner's double, combined.
+template <int CTRL, bool MAX>
+__device__ __forceinline__ double dpp_fold(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, int(b), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), CTRL, 0xF, 0xF, false);
+  const double o = __longlong_as_double((long long)(((unsigned long long)unsigned(hi) << 32) |
+                                                    unsigned(lo)));
+  if constexpr (MAX) return o <= v ? v : o;  // a NaN wins
+  return v + o;
+}
+
+// Sum (MAX: maximum) over a row of 16 lanes, in every lane.
+template <bool MAX>
+__device__ __forceinline__ double row_fold(double v) {
+  v = dpp_fold<0xB1, MAX>(v);
+  v = dpp_fold<0x4E, MAX>(v);
+  v = dpp_fold<0x141, MAX>(v);
+  return dpp_fold<0x140, MAX>(v);
+}
+
+// Sum over an aligned group of G = 4, 16 or 64 lanes without LDS traffic, in
+// every lane of the group.
+template <int G>
+__device__ __forceinline__ double lanes_sum_f64(double v) {
+  static_assert(G == 4 || G == 16 || G == kWave, "whole quads, rows or waves");
+  v = dpp_fold<0xB1, false>(v);
+  v = dpp_fold<0x4E, false>(v);
+  if constexpr (G >= 16) {
+    v = dpp_fold<0x141, false>(v);
+    v = dpp_fold<0x140, false>(v);
+  }
+  if constexpr (G == kWave) {
+    const long long b = __double_as_longlong(v);
+    double t = 0.0;
+#pragma unroll
+    for (int r = 0; r < kWave; r += 16) {
+      const unsigned lo = unsigned(__builtin_amdgcn_readlane(int(b), r));
+      const unsigned hi = unsigned(__builtin_amdgcn_readlane(int(b >> 32), r));
+      t += __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    }
+    v = t;
+  }
+  return v;
+}
+
 // Rounding error of a + b (TwoSum, exact in round-to-nearest).
 __device__ __forceinline__ float twosum_err(float a, float b) {
   const float s = a + b;

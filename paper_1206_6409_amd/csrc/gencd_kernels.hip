@@ -21,6 +21,8 @@
 // host involvement).
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "gencd_common.hpp"
 #include "gencd_kernels.hpp"
 
@@ -2077,6 +2079,218 @@ __global__ __launch_bounds__(kBlock) void k_rho_scale(int64_t k, int64_t n, cons
   for (int64_t i = tid; i < n; i += nt) s64[i] = 0.0;
 }
 
+// Dense products for the power iteration with the row vector in LDS.
+//
+// With x dense, s = X x by global FP64 atomics runs at the rate of those
+// atomics (21 per ns on MI355X, whatever the layout: 1175 us for 25 M
+// nonzeros), and U = X^T s at the rate of L2 gathers (123 us).  Here the rows
+// are cut into nb <= kRhoMaxBlocks blocks of at most kRhoRows rows, whose
+// slice of the row vector one workgroup holds in LDS as FP64.  spmv: a
+// workgroup adds the entries of its columns (an nnz-balanced chunk) that lie
+// in its row block into LDS and stores the slice as one of `parts` partial
+// vectors, which k_rho_fold adds up; no global atomics.  cols: a workgroup
+// walks the blocks one after the other and keeps its columns' sums in LDS.
+// Rows are sorted inside a column, so a block's entries are one range, found
+// once per estimate by k_rho_cut.  Both then stream X once: at 25 M nonzeros
+// (n = 25 000, 200 MB) 77 and 75 us, 2.6 TB/s of the 4.7 TB/s a large copy
+// reaches; a 20-step estimate 26.5 -> 3.5 ms.
+constexpr int kRhoRows = 19456;       // 152 KB of LDS
+constexpr int kRhoMaxBlocks = 3;      // cuts live in two arrays of k
+constexpr int kRhoThreads = 1024;
+constexpr int kRhoChunkCols = 512;    // columns a workgroup of k_rho_cols takes at a time
+
+struct RhoArgs {
+  const int64_t *col_ptr;
+  const int32_t *row_idx;
+  const float *val;
+  const int32_t *live;    // non-empty columns
+  int32_t *cut0, *cut1;   // [k] first entry (offset in its column) of row block 1, 2
+  int64_t n, k_live, nnz;
+  int32_t nb, rows, parts, G;
+};
+
+__global__ __launch_bounds__(kBlock) void k_rho_cut(RhoArgs a) {
+  for (int64_t q = int64_t(blockIdx.x) * kBlock + threadIdx.x; q < a.k_live;
+       q += int64_t(gridDim.x) * kBlock) {
+    const int32_t j = a.live[q];
+    const int64_t b = a.col_ptr[j];
+    const int32_t len = int32_t(a.col_ptr[j + 1] - b);
+    for (int32_t c = 1; c < a.nb; ++c) {
+      int32_t lo = 0, hi = len;  // first entry with row >= c * rows
+      while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (int64_t(a.row_idx[b + mid]) < int64_t(c) * a.rows) lo = mid + 1; else hi = mid;
+      }
+      (c == 1 ? a.cut0 : a.cut1)[j] = lo;
+    }
+  }
+}
+
+// kRhoCols columns of a lane group at once (live positions q, q + step, ...
+// below end): columns, entry ranges [lo, hi) of row block b, and the first
+// G * kUnroll entries of each.  Taken together, the loads of one stage of the
+// chain position -> column -> bounds -> entries are in flight at the same
+// time; one column after the other took 120 us instead of 77.
+constexpr int kRhoCols = 4;
+struct RhoBatch {
+  int32_t j[kRhoCols];
+  uint32_t lo[kRhoCols], hi[kRhoCols];
+  int32_t ri[kRhoCols][kUnroll];
+  float vv[kRhoCols][kUnroll];
+};
+
+template <int G>
+__device__ __forceinline__ void rho_load(const RhoArgs &a, int32_t b, int64_t q, int64_t step,
+                                         int64_t end, int lane, RhoBatch &t) {
+#pragma unroll
+  for (int v = 0; v < kRhoCols; ++v) t.j[v] = a.live[q + v * step < end ? q + v * step : q];
+#pragma unroll
+  for (int v = 0; v < kRhoCols; ++v) {
+    const uint32_t beg = uint32_t(a.col_ptr[t.j[v]]);
+    t.lo[v] = b == 0 ? beg : beg + uint32_t((b == 1 ? a.cut0 : a.cut1)[t.j[v]]);
+    t.hi[v] = b + 1 == a.nb ? uint32_t(a.col_ptr[t.j[v] + 1])
+                            : beg + uint32_t((b == 0 ? a.cut0 : a.cut1)[t.j[v]]);
+    if (q + v * step >= end) t.hi[v] = t.lo[v];
+  }
+#pragma unroll
+  for (int v = 0; v < kRhoCols; ++v) {
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const uint32_t e = t.lo[v] + uint32_t(u * G + lane);
+      const uint32_t at = e < t.hi[v] ? e : uint32_t(a.nnz - 1);
+      const int32_t r = a.row_idx[at];
+      t.vv[v][u] = a.val[at];
+      t.ri[v][u] = e < t.hi[v] ? r : -1;
+    }
+  }
+}
+
+// First live column whose entries start at or after `target` (the chunks'
+// bounds): a search over 64 probes a round by the first wave.
+__device__ __forceinline__ int64_t rho_bound(const RhoArgs &a, int64_t target) {
+  int64_t lo = 0, hi = a.k_live;  // the answer is in [lo, hi]
+  while (hi > lo) {
+    const int64_t step = (hi - lo + kWave - 1) / kWave;
+    const int64_t q = lo + step * (int64_t(threadIdx.x) & (kWave - 1));
+    const bool below = q < hi && a.col_ptr[a.live[q]] < target;
+    const int c = __popcll(__ballot(below));  // the probes are ordered
+    if (c == 0) return lo;
+    const int64_t nlo = lo + step * (c - 1) + 1;
+    hi = lo + step * c < hi ? lo + step * c : hi;
+    lo = nlo;
+  }
+  return lo;
+}
+
+template <int G>
+__global__ __launch_bounds__(kRhoThreads) void k_rho_spmv(RhoArgs a, const double *x,
+                                                           double *part) {
+  __shared__ double sl[kRhoRows];
+  __shared__ int64_t bound[2];
+  const int32_t b = int32_t(blockIdx.x) % a.nb, c = int32_t(blockIdx.x) / a.nb;
+  const int64_t r0 = int64_t(b) * a.rows;
+  const int32_t m = int32_t(a.n - r0 < a.rows ? a.n - r0 : a.rows);
+  for (int32_t i = threadIdx.x; i < m; i += kRhoThreads) sl[i] = 0.0;
+  if (threadIdx.x < 2 * kWave) {
+    const int w = int(threadIdx.x) / kWave;
+    const int64_t v = c + w == a.parts ? a.k_live : rho_bound(a, a.nnz * (c + w) / a.parts);
+    if ((threadIdx.x & (kWave - 1)) == 0) bound[w] = v;
+  }
+  __syncthreads();
+  const int lane = int(threadIdx.x) & (G - 1);
+  constexpr int64_t NG = kRhoThreads / G;
+  const int64_t q1 = bound[1];
+  for (int64_t q = bound[0] + threadIdx.x / G; q < q1; q += NG * kRhoCols) {
+    RhoBatch t;
+    rho_load<G>(a, b, q, NG, q1, lane, t);
+#pragma unroll
+    for (int v = 0; v < kRhoCols; ++v) {
+      const double xj = x[t.j[v]];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u)
+        if (t.ri[v][u] >= 0) atomicAdd(&sl[t.ri[v][u] - r0], xj * double(t.vv[v][u]));
+#pragma unroll 1
+      for (uint32_t e = t.lo[v] + uint32_t(G * kUnroll + lane); e < t.hi[v]; e += G)
+        atomicAdd(&sl[a.row_idx[e] - r0], xj * double(a.val[e]));
+    }
+  }
+  __syncthreads();
+  for (int32_t i = threadIdx.x; i < m; i += kRhoThreads) part[int64_t(c) * a.n + r0 + i] = sl[i];
+}
+
+__global__ __launch_bounds__(kBlock) void k_rho_fold(int64_t n, int32_t parts, const double *part,
+                                                      double *s64) {
+  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n;
+       i += int64_t(gridDim.x) * kBlock) {
+    double t = 0.0;
+#pragma unroll 8
+    for (int32_t c = 0; c < parts; ++c) t += part[int64_t(c) * n + i];
+    s64[i] = t;
+  }
+}
+
+template <int G>
+__global__ __launch_bounds__(kRhoThreads) void k_rho_cols(RhoArgs a, const double *s64, double *u) {
+  __shared__ double sl[kRhoRows];
+  __shared__ double acc[kRhoChunkCols];
+  __shared__ int64_t bound[2];
+  const int32_t c = blockIdx.x, nc = gridDim.x;
+  if (threadIdx.x < 2 * kWave) {
+    const int w = int(threadIdx.x) / kWave;
+    const int64_t v = c + w == nc ? a.k_live : rho_bound(a, a.nnz * (c + w) / nc);
+    if ((threadIdx.x & (kWave - 1)) == 0) bound[w] = v;
+  }
+  __syncthreads();
+  const int lane = int(threadIdx.x) & (G - 1);
+  constexpr int64_t NG = kRhoThreads / G;
+  const int64_t q1 = bound[1];
+  for (int64_t q0 = bound[0]; q0 < q1; q0 += kRhoChunkCols) {
+    const int64_t qe = q0 + kRhoChunkCols < q1 ? q0 + kRhoChunkCols : q1;
+    for (int32_t b = 0; b < a.nb; ++b) {
+      const int64_t r0 = int64_t(b) * a.rows;
+      const int32_t m = int32_t(a.n - r0 < a.rows ? a.n - r0 : a.rows);
+      if (a.nb > 1 || q0 == bound[0]) {
+        __syncthreads();  // the previous block's slice has been read
+        for (int32_t i = threadIdx.x; i < m; i += kRhoThreads) sl[i] = s64[r0 + i];
+        __syncthreads();
+      }
+      for (int64_t q = q0 + threadIdx.x / G; q < qe; q += NG * kRhoCols) {
+        RhoBatch t;
+        rho_load<G>(a, b, q, NG, qe, lane, t);
+#pragma unroll
+        for (int v = 0; v < kRhoCols; ++v) {
+          double s = 0.0;
+#pragma unroll
+          for (int k = 0; k < kUnroll; ++k) {
+            if (!__any(t.ri[v][k] >= 0)) break;
+            if (t.ri[v][k] >= 0) s += double(t.vv[v][k]) * sl[t.ri[v][k] - r0];
+          }
+#pragma unroll 1
+          for (uint32_t e = t.lo[v] + uint32_t(G * kUnroll + lane); e < t.hi[v]; e += G)
+            s += double(a.val[e]) * sl[a.row_idx[e] - r0];
+          s = lanes_sum_f64<G>(s);
+          const int64_t qv = q + v * NG;
+          if (lane == 0 && qv < qe) {  // the same lane takes the column in every block
+            const double f = b == 0 ? s : acc[qv - q0] + s;
+            acc[qv - q0] = f;
+            if (b + 1 == a.nb) u[t.j[v]] = f;
+          }
+        }
+      }
+    }
+  }
+}
+
+template <int G>
+static void launch_rho_products(const RhoArgs &a, const double *x, double *part, double *s64,
+                                double *u, hipStream_t s) {
+  hipLaunchKernelGGL(k_rho_spmv<G>, dim3(unsigned(a.parts * a.nb)), dim3(kRhoThreads), 0, s, a, x,
+                     part);
+  hipLaunchKernelGGL(k_rho_fold, dim3(grid_for(a.n)), dim3(kBlock), 0, s, a.n, a.parts, part, s64);
+  const unsigned cg = unsigned(a.nnz / 8192 < 1 ? 1 : (a.nnz / 8192 > 256 ? 256 : a.nnz / 8192));
+  hipLaunchKernelGGL(k_rho_cols<G>, dim3(cg), dim3(kRhoThreads), 0, s, a, s64, u);
+}
+
 int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws &ws, int64_t k_live,
                int iters, hipStream_t s) {
   if (!ws.rho_dinv || iters < 1 || iters > kRhoMaxIters || k_live <= 0) return GENCD_ERR_INVALID_ARG;
@@ -2084,10 +2298,44 @@ int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws 
   unsigned blocks;
   int32_t nl;
   two_class_grid(n_short, n_lpieces, 8, &blocks, &nl);
+  // The LDS form: the partial row vectors take the part of the workspace that
+  // only the epochs use (desc_s up to acc, contiguous), so its size bounds
+  // their number.  Below kRhoMinParts of them, or of 8192 entries for each,
+  // too few workgroups would stream X and the atomics are as fast.
+  RhoArgs ra{};
+  ra.col_ptr = X->col_ptr;
+  ra.row_idx = X->row_idx;
+  ra.val = X->val;
+  ra.live = ws.live;
+  ra.cut0 = ws.tmp_cnt;
+  ra.cut1 = ws.tmp_cnt2;
+  ra.n = X->n;
+  ra.k_live = k_live;
+  ra.nnz = X->nnz;
+  ra.nb = int32_t(std::min<int64_t>((X->n + kRhoRows - 1) / kRhoRows, 1 << 20));
+  ra.rows = int32_t((X->n + ra.nb - 1) / ra.nb);
+  double *part = reinterpret_cast<double *>(ws.desc_s);
+  const int64_t room = reinterpret_cast<char *>(ws.acc + X->k) - reinterpret_cast<char *>(ws.desc_s);
+  int64_t parts = room / int64_t(sizeof(double)) / X->n;
+  parts = std::min<int64_t>(parts, X->nnz / 8192);
+  parts = std::min<int64_t>(parts, 256 / ra.nb);
+  constexpr int64_t kRhoMinParts = 8;
+  const bool lds = ra.nb <= kRhoMaxBlocks && parts >= kRhoMinParts;
+  ra.parts = int32_t(parts);
+  const double per = double(X->nnz) / double(k_live) / double(ra.nb);  // entries per range
   hipLaunchKernelGGL(k_rho_init, dim3(grid_for(nk)), dim3(kBlock), 0, s, X->k, X->n, ws.g64,
                      ws.rho_dinv, ws.rho_x, 1.0 / sqrt(double(k_live)), ws.z64, ws.rho_hist, iters);
+  if (lds && ra.nb > 1)
+    hipLaunchKernelGGL(k_rho_cut, dim3(grid_for(k_live)), dim3(kBlock), 0, s, ra);
   for (int t = 0; t < iters; ++t) {
-    if (n_short + n_lpieces > 0) {
+    if (lds) {
+      if (per > 96.0)
+        launch_rho_products<64>(ra, ws.rho_x, part, ws.z64, ws.g64, s);
+      else if (per > 24.0)
+        launch_rho_products<16>(ra, ws.rho_x, part, ws.z64, ws.g64, s);
+      else
+        launch_rho_products<4>(ra, ws.rho_x, part, ws.z64, ws.g64, s);
+    } else if (n_short + n_lpieces > 0) {
       hipLaunchKernelGGL((k_check_spmv<8, double>), dim3(blocks), dim3(kBlock), 0, s, X->row_idx,
                          X->val, ws.desc_all_s, n_short, ws.desc_all_l, n_lpieces, nl, ws.rho_x,
                          ws.z64);

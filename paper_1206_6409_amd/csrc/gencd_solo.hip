@@ -59,26 +59,6 @@ __device__ __forceinline__ void lds_barrier() {
   }
 }
 
-// One step of a reduction inside a DPP row: the partner's double, combined.
-template <int CTRL, bool MAX>
-__device__ __forceinline__ double dpp_fold(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, int(b), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), CTRL, 0xF, 0xF, false);
-  const double o = __longlong_as_double((long long)(((unsigned long long)unsigned(hi) << 32) |
-                                                    unsigned(lo)));
-  if constexpr (MAX) return o <= v ? v : o;  // a NaN wins
-  return v + o;
-}
-
-template <bool MAX>
-__device__ __forceinline__ double row_fold(double v) {
-  v = dpp_fold<0xB1, MAX>(v);
-  v = dpp_fold<0x4E, MAX>(v);
-  v = dpp_fold<0x141, MAX>(v);
-  return dpp_fold<0x140, MAX>(v);
-}
-
 // Block sums (the first NS values) and maxima (the rest) of NV doubles;
 // every thread gets them.  Rows of 16 lanes fold by DPP moves, their results
 // go through LDS.
