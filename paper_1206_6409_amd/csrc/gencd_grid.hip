@@ -1,0 +1,456 @@
+// Whole epochs of a mid-size problem on a grid of resident workgroups.
+//
+// A window of a few thousand columns is a few tens of thousands of entries:
+// about two microseconds of dependent loads and atomics, but two launches
+// with a drained device between them (11 us an iteration on MI355X, of which
+// the two kernels' own chains of loads are most).  Here one launch runs all
+// windows of an epoch.  Its workgroups meet at a barrier where the two-launch
+// form has a kernel boundary, and a wave loads the descriptors, entries and
+// weights of its share of the next windows while it works on the current one,
+// so what is left between two barriers is the row gather, the reduction and
+// the step, or the atomics.
+//
+// What bounds it: the two barriers (about 1.2 us each) and the chains between
+// them.  Per window, two launches -> this: 2k entries 7.3 -> 4.6 us, 15k 9.9
+// -> 7.0, 61k (|J| = 4096 of the text-like matrix) 11.0 -> 10.0, 122k 12.7 ->
+// 15.0.  Coloring, 560 windows of 10k entries: 7.4 -> 5.2 us.
+//
+// Memory between workgroups.  The eight XCDs have an L2 each, so everything
+// one workgroup writes and another reads inside the launch goes through
+// agent-scope accesses: the rows are read with the agent-scope cache policy
+// and changed by atomics (Coloring: by agent-scope stores), partial sums and
+// barrier flags are agent-scope atomics.  A wave waits for its own accesses
+// before its workgroup raises its flag.  What the launch only reads (matrix,
+// order, curvature) takes the ordinary path, and a column's weight is read
+// and written by the waves of that column alone, once per epoch.
+//
+// Residency.  The workgroups that meet are those that enrolled before the
+// first of them closed the list; a workgroup that starts later leaves at
+// once, so a device busy with other work gives a smaller grid, never a wait
+// for a workgroup that is not running.  Every wait is bounded; a wait that
+// runs out raises an error flag that the host reads with the next check.
+#include <algorithm>
+
+#include "gencd_common.hpp"
+#include "gencd_kernels.hpp"
+
+namespace gencd {
+
+template <typename T>
+__device__ __forceinline__ T agent_load(const T *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void agent_store(T *p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+constexpr int kGridPolls = 1 << 22;      // about 2 s; a barrier takes about a microsecond
+constexpr int kEnrollPolls = 4096;       // about 2 ms for the whole grid to start
+constexpr int32_t kClosed = 1 << 20;     // above any number of workgroups
+
+// Members of the grid: this workgroup's index (-1: not one of them).
+__device__ __forceinline__ int grid_enroll(GridCtl *c, int *sm, int &members) {
+  if (threadIdx.x == 0) {
+    int idx = atomicAdd(&c->count, 1), m = 0;
+    if (idx == 0) {
+      for (int p = 0; p < kEnrollPolls && agent_load(&c->count) < int(gridDim.x); ++p)
+        __builtin_amdgcn_s_sleep(2);
+      m = atomicAdd(&c->count, kClosed);
+      agent_store(&c->members, m);
+    } else if (idx < kClosed) {
+      for (int p = 0; p < kGridPolls && (m = agent_load(&c->members)) == 0; ++p)
+        __builtin_amdgcn_s_sleep(1);
+    }
+    sm[0] = idx < m ? idx : -1;
+    sm[1] = m;
+  }
+  __syncthreads();
+  members = sm[1];
+  return sm[0];
+}
+
+// Every member has arrived at `round`, and its accesses before have been
+// performed.  The flags are packed, so that the first wave reads all of them
+// with one or two loads; one hop, no counter that the arrivals queue on.
+__device__ __forceinline__ bool grid_barrier(GridCtl *c, unsigned long long *bad, int me, int members,
+                                             int round, int *sm) {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    if (threadIdx.x == 0) agent_store(&c->flag[me], round);
+    int p = 0;
+    bool ok;
+    do {
+      ok = true;
+      for (int i = int(threadIdx.x); i < members; i += kWave)
+        ok = ok && agent_load(&c->flag[i]) >= round;
+    } while (!__all(ok) && ++p < kGridPolls);
+    if (threadIdx.x == 0) {
+      sm[0] = p < kGridPolls;
+      if (p >= kGridPolls) atomicOr(bad, 16ull);
+    }
+  }
+  __syncthreads();
+  return sm[0] != 0;
+}
+
+typedef int int4v __attribute__((ext_vector_type(4)));
+
+// The packed rows as a buffer: 16-byte loads with the agent-scope policy.
+struct Rows {
+  __amdgpu_buffer_rsrc_t r;
+};
+__device__ __forceinline__ float4 row_load(const Rows &z, int32_t i) {
+  const int4v v = __builtin_amdgcn_raw_buffer_load_b128(z.r, i * 16, 0, 16);
+  return make_float4(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z), 0.0f);
+}
+
+// Compensated update of a row that this lane owns in the window (columns of a
+// colour class have disjoint rows), from its values at the window's start.
+__device__ __forceinline__ void row_store(float4 *zs, int32_t i, float hi, float lo, float d,
+                                          float v) {
+  const float p = d * v;
+  const float pe = fmaf(d, v, -p);
+  const float h = hi + p, l = lo + (twosum_err(hi, p) + pe);
+  const unsigned long long b = (static_cast<unsigned long long>(__float_as_uint(l)) << 32) |
+                               static_cast<unsigned long long>(__float_as_uint(h));
+  agent_store(reinterpret_cast<unsigned long long *>(zs + i), b);
+}
+
+// One wave's work unit of a window: 64 / GS short columns, or one piece of a
+// long column; kUnroll entries per lane either way.
+struct Unit {
+  int4 d;         // the group's descriptor (length 0: nothing to do)
+  int32_t pf, pe; // split column: its pieces [pf, pe)
+  float w, c;
+  int32_t ri[kUnroll];
+  float vv[kUnroll];
+};
+
+// 16 waves with one unit each beat 8 waves with two and 4 with three by 2 to
+// 10% (the units of a wave follow each other through its instructions).
+constexpr int kGridThreads = 1024;
+constexpr int kUnits = 1;  // units a wave holds in registers; more are taken from memory
+
+struct WindowPos {
+  int32_t P0, P1, q0, q1;  // positions and long pieces
+};
+
+template <int GS>
+struct GridWave {
+  const IterArgs &a;
+  int wave, nw, lane;
+
+  // Bounds of the windows from `base` on, one per lane, read back by
+  // readlane: a load per window would have to be waited for at its first use.
+  int32_t base, wb, wo;
+  __device__ __forceinline__ void bounds(int32_t t, int32_t T) {
+    base = t;
+    const int32_t i = t + lane < T ? t + lane : T;
+    wb = a.wbl[i];
+    wo = a.win_off ? a.win_off[i] : 0;
+  }
+  __device__ __forceinline__ WindowPos window(int32_t t, int32_t T) {
+    WindowPos w{0, 0, 0, 0};
+    if (t >= T) return w;
+    if (t - base > kWave - 2) bounds(t, T);
+    if (a.win_off) {
+      w.P0 = __builtin_amdgcn_readlane(wo, t - base);
+      w.P1 = __builtin_amdgcn_readlane(wo, t - base + 1);
+    } else {
+      w.P0 = t * a.S;
+      w.P1 = a.k_live - w.P0 < a.S ? a.k_live : w.P0 + a.S;
+    }
+    w.q0 = __builtin_amdgcn_readlane(wb, t - base);
+    w.q1 = __builtin_amdgcn_readlane(wb, t - base + 1);
+    return w;
+  }
+  __device__ __forceinline__ int32_t units(const WindowPos &w) const {
+    return w.q1 - w.q0 + (w.P1 - w.P0 + kWave / GS - 1) / (kWave / GS);
+  }
+  // long unit: one piece per wave
+  __device__ __forceinline__ bool is_long(const WindowPos &w, int32_t u) const {
+    return u < w.q1 - w.q0;
+  }
+  __device__ __forceinline__ int4 desc(const WindowPos &w, int32_t u) const {
+    if (is_long(w, u)) return a.desc_l[w.q0 + u];
+    const int32_t p = w.P0 + (u - (w.q1 - w.q0)) * (kWave / GS) + lane / GS;
+    return p < w.P1 ? a.desc_s[p] : make_int4(0, 0, 0, 0);
+  }
+  // entries (first kUnroll of a lane), weight, curvature of a unit
+  __device__ __forceinline__ void fill(bool lng, Unit &x) const {
+    const int32_t len = x.d.w & 0x7FFFFFFF;
+    const uint32_t beg = uint32_t(x.d.x);
+    const int32_t g = lng ? kWave : GS, l = lng ? lane : (lane & (GS - 1));
+    x.w = a.w[x.d.y];
+    x.c = a.c[x.d.y];
+    // nothing here may use a loaded value: the loads stay in flight
+    if (lng) {  // (only split columns read these)
+      x.pf = a.loff[x.d.z];
+      x.pe = a.loff[x.d.z + 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int32_t e = u * g + l;
+      const int64_t at = int64_t(beg) + (e < len ? e : 0);
+      x.ri[u] = a.row_idx[at];
+      x.vv[u] = a.val[at];
+    }
+  }
+  // whether entry u of this lane exists (past the end ri, vv repeat the first)
+  __device__ __forceinline__ bool has(bool lng, const Unit &x, int u) const {
+    return u * (lng ? kWave : GS) + (lng ? lane : (lane & (GS - 1))) < (x.d.w & 0x7FFFFFFF);
+  }
+};
+
+// Sum of the four row sums of a wave, in every lane.
+__device__ __forceinline__ float rows_sum(float x) {
+  const int b = __float_as_int(x);
+  return (__int_as_float(__builtin_amdgcn_readlane(b, 0)) +
+          __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
+         (__int_as_float(__builtin_amdgcn_readlane(b, 32)) +
+          __int_as_float(__builtin_amdgcn_readlane(b, 48)));
+}
+
+// Sum of a unit's lanes in every lane: GS lanes of a short column, or the wave.
+template <int GS>
+__device__ __forceinline__ float unit_sum(bool lng, float s) {
+  if constexpr (GS <= 16) {
+    s = row_group_sum<GS>(s);
+    if (!lng) return s;  // uniform over the wave
+    if constexpr (GS < 16) {
+      if constexpr (GS < 8) s += dpp_move<0x141>(s);
+      s += dpp_move<0x140>(s);
+    }
+    return rows_sum(s);
+  } else {
+    return lng ? group_sum<kWave>(s) : group_sum<GS>(s);
+  }
+}
+
+// Partial sums of a split column, in piece order (every piece's wave gets
+// the same value).
+__device__ __forceinline__ float split_total(const float *part, int32_t pf, int32_t np, int lane) {
+  float t = 0.0f;
+  for (int32_t u0 = 0; u0 < np; u0 += kWave * kUnroll) {
+    float v[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int32_t i = u0 + u * kWave + lane;
+      v[u] = i < np ? agent_load(&part[pf + i]) : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) t += v[u];
+  }
+  return rows_sum(row_group_sum<16>(t));
+}
+
+// MODE 0: Jacobi windows, atomic scatter.  MODE 1: Coloring (rows of a window
+// disjoint): compensated stores.
+template <int GS, int MODE>
+__global__ __launch_bounds__(kGridThreads) void k_epoch_grid(IterArgs a, GridCtl *ctl,
+                                                        unsigned long long *bad, int32_t T) {
+  __shared__ int sm[2];
+  int members;
+  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(ctl, sm, members));
+  members = __builtin_amdgcn_readfirstlane(members);
+  if (me < 0) return;
+  // waves numbered slot-major: consecutive units go to different workgroups
+  const int lane = int(threadIdx.x) & (kWave - 1);
+  const int slot = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+  GridWave<GS> gw{a, slot * members + me, members * (kGridThreads / kWave), lane, 0, 0, 0};
+  gw.bounds(0, T);
+  const Rows z{__builtin_amdgcn_make_buffer_rsrc(a.zs, 0, int(a.nrows * 16), 0x00027000)};
+  Unit cur[kUnits], nxt[kUnits];
+  WindowPos wp = gw.window(0, T), wn = gw.window(1, T);
+#pragma unroll
+  for (int k = 0; k < kUnits; ++k) {
+    const int32_t u = gw.wave + k * gw.nw;
+    cur[k].d = u < gw.units(wp) ? gw.desc(wp, u) : make_int4(0, 0, 0, 0);
+    nxt[k].d = u < gw.units(wn) ? gw.desc(wn, u) : make_int4(0, 0, 0, 0);
+  }
+#pragma unroll
+  for (int k = 0; k < kUnits; ++k) gw.fill(gw.is_long(wp, gw.wave + k * gw.nw), cur[k]);
+  int round = 0;
+  for (int32_t t = 0; t < T; ++t) {
+    const WindowPos w2 = gw.window(t + 2, T);
+    const int32_t nu = gw.units(wp);
+    if (nu == 0) {  // an empty colour class: the same decision in every workgroup
+      wp = wn;
+      wn = w2;
+#pragma unroll
+      for (int k = 0; k < kUnits; ++k) {
+        const int32_t u = gw.wave + k * gw.nw;
+        cur[k].d = nxt[k].d;
+        if (u < gw.units(wp)) gw.fill(gw.is_long(wp, u), cur[k]);
+        nxt[k].d = u < gw.units(wn) ? gw.desc(wn, u) : make_int4(0, 0, 0, 0);
+      }
+      continue;
+    }
+    // rows of the units in registers
+    float zh[kUnits][kUnroll], zl[kUnits][kUnroll], yy[kUnits][kUnroll];
+#pragma unroll
+    for (int k = 0; k < kUnits; ++k) {
+      if (gw.wave + k * gw.nw >= nu) break;  // uniform over the wave
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const float4 r = row_load(z, cur[k].ri[u]);
+        zh[k][u] = r.x;
+        zl[k][u] = r.y;
+        yy[k][u] = r.z;
+      }
+    }
+    // the next window's entries, and the descriptors of the one after
+    int4 dd[kUnits];
+#pragma unroll
+    for (int k = 0; k < kUnits; ++k) {
+      const int32_t u = gw.wave + k * gw.nw;
+      if (u < gw.units(wn)) gw.fill(gw.is_long(wn, u), nxt[k]);
+      dd[k] = u < gw.units(w2) ? gw.desc(w2, u) : make_int4(0, 0, 0, 0);
+    }
+    // Propose
+    float d[kUnits];
+#pragma unroll
+    for (int k = 0; k < kUnits; ++k) {
+      d[k] = 0.0f;
+      const int32_t u = gw.wave + k * gw.nw;
+      if (u >= nu) break;
+      const bool lng = gw.is_long(wp, u);
+      float s = 0.0f;
+#pragma unroll
+      for (int v = 0; v < kUnroll; ++v)
+        if (gw.has(lng, cur[k], v)) s += cur[k].vv[v] * dloss_f32(a.loss, yy[k][v], zh[k][v] + zl[k][v]);
+      s = unit_sum<GS>(lng, s);
+      if (lng && cur[k].d.w >= 0) {
+        if (lane == 0) agent_store(&a.gacc[wp.q0 + u], s);
+      } else {
+        float ph;
+        propose_f32(s / a.n_f, cur[k].c, cur[k].w, a.lam, d[k], ph);
+      }
+    }
+    // units beyond the registers: increments of short and one-piece columns
+    // to delta (read back by the same lanes), partial sums to gacc
+    for (int32_t u = gw.wave + kUnits * gw.nw; u < nu; u += gw.nw) {
+      Unit x;
+      const bool lng = gw.is_long(wp, u);
+      x.d = gw.desc(wp, u);
+      gw.fill(lng, x);
+      float s = 0.0f;
+#pragma unroll
+      for (int v = 0; v < kUnroll; ++v) {
+        const float4 r = row_load(z, x.ri[v]);
+        if (gw.has(lng, x, v)) s += x.vv[v] * dloss_f32(a.loss, r.z, r.x + r.y);
+      }
+      s = unit_sum<GS>(lng, s);
+      if (lng && x.d.w >= 0) {
+        if (lane == 0) {
+          agent_store(&a.gacc[wp.q0 + u], s);
+          // the weight before any wave of the column updates it
+          agent_store(&a.wsnap[x.d.z - wp.P0], x.w);
+        }
+      } else {
+        float de, ph;
+        propose_f32(s / a.n_f, x.c, x.w, a.lam, de, ph);
+        if ((x.d.w & 0x7FFFFFFF) > 0) a.delta[x.d.z - wp.P0] = de;
+      }
+    }
+    if (!grid_barrier(ctl, bad, me, members, ++round, sm)) return;
+    // Update
+#pragma unroll
+    for (int k = 0; k < kUnits; ++k) {
+      const int32_t u = gw.wave + k * gw.nw;
+      if (u >= nu) break;
+      const bool lng = gw.is_long(wp, u);
+      const bool split = lng && cur[k].d.w >= 0;
+      if (split) {
+        float ph;
+        const float g = split_total(a.gacc, cur[k].pf, cur[k].pe - cur[k].pf, lane) / a.n_f;
+        propose_f32(g, cur[k].c, cur[k].w, a.lam, d[k], ph);
+      }
+      if (d[k] == 0.0f || (cur[k].d.w & 0x7FFFFFFF) == 0) continue;
+      const bool owner = lng ? lane == 0 && (!split || wp.q0 + u == cur[k].pf)
+                             : (lane & (GS - 1)) == 0;
+      if (owner) a.w[cur[k].d.y] = cur[k].w + d[k];
+#pragma unroll
+      for (int v = 0; v < kUnroll; ++v) {
+        const int32_t i = cur[k].ri[v];
+        if (!gw.has(lng, cur[k], v)) continue;
+        if (MODE == 0)
+          atomicAdd(&a.zs[i].y, d[k] * cur[k].vv[v]);
+        else
+          row_store(a.zs, i, zh[k][v], zl[k][v], d[k], cur[k].vv[v]);
+      }
+    }
+    for (int32_t u = gw.wave + kUnits * gw.nw; u < nu; u += gw.nw) {
+      Unit x;
+      const bool lng = gw.is_long(wp, u);
+      x.d = gw.desc(wp, u);
+      gw.fill(lng, x);
+      const bool split = lng && x.d.w >= 0;
+      float de, ph;
+      if (split) {
+        const float g = split_total(a.gacc, x.pf, x.pe - x.pf, lane) / a.n_f;
+        x.w = agent_load(&a.wsnap[x.d.z - wp.P0]);
+        propose_f32(g, x.c, x.w, a.lam, de, ph);
+      } else {
+        de = (x.d.w & 0x7FFFFFFF) > 0 ? a.delta[x.d.z - wp.P0] : 0.0f;
+      }
+      if (de == 0.0f) continue;
+      const bool owner = lng ? lane == 0 && (!split || wp.q0 + u == x.pf)
+                             : (lane & (GS - 1)) == 0;
+      if (owner) a.w[x.d.y] = x.w + de;
+#pragma unroll
+      for (int v = 0; v < kUnroll; ++v) {
+        const int32_t i = x.ri[v];
+        if (!gw.has(lng, x, v)) continue;
+        if (MODE == 0) {
+          atomicAdd(&a.zs[i].y, de * x.vv[v]);
+        } else {
+          const float4 r = row_load(z, i);
+          row_store(a.zs, i, r.x, r.y, de, x.vv[v]);
+        }
+      }
+    }
+    if (!grid_barrier(ctl, bad, me, members, ++round, sm)) return;
+    wp = wn;
+    wn = w2;
+#pragma unroll
+    for (int k = 0; k < kUnits; ++k) {
+      cur[k] = nxt[k];
+      nxt[k].d = dd[k];
+    }
+  }
+}
+
+// Workgroups for windows of `nnz` entries on average.  A barrier takes 0.9 us
+// among 32, 1.2 among 64 and 1.8 among 128 (every member reads every flag);
+// more of them gather and scatter faster.  Per window, 32 / 64 / 128: 2k
+// entries 4.6 / 4.8 / 5.9 us, 8k 6.1 / 6.1 / 7.0, 31k 8.6 / 8.1 / 8.6, 61k
+// 13.0 / 10.0 / 9.9.
+static unsigned grid_size(double nnz) { return nnz <= 8192.0 ? 32 : 64; }
+
+template <int GS>
+static void launch_grid_g(const IterArgs &a, int mode, GridCtl *ctl, unsigned long long *bad,
+                          int32_t T, unsigned m, hipStream_t s) {
+  if (mode == 1)
+    hipLaunchKernelGGL((k_epoch_grid<GS, 1>), dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, T);
+  else
+    hipLaunchKernelGGL((k_epoch_grid<GS, 0>), dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, T);
+}
+
+int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
+                      unsigned long long *bad, int64_t T, double nnz, hipStream_t s) {
+  if (a.piece > kWave * kUnroll || T < 1 || a.k_live < 1 || a.nrows * 16 > INT32_MAX)
+    return GENCD_ERR_INVALID_ARG;
+  const unsigned m = grid_size(nnz);
+  switch (group) {
+    case 4: launch_grid_g<4>(a, mode, ctl, bad, int32_t(T), m, s); break;
+    case 8: launch_grid_g<8>(a, mode, ctl, bad, int32_t(T), m, s); break;
+    case 16: launch_grid_g<16>(a, mode, ctl, bad, int32_t(T), m, s); break;
+    default: launch_grid_g<32>(a, mode, ctl, bad, int32_t(T), m, s); break;
+  }
+  return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
+}
+
+}  // namespace gencd

@@ -381,16 +381,20 @@ __global__ __launch_bounds__(kBlock) void k_col_counts(const int64_t *col_ptr, i
     live_flag[j] = m > 0 ? 1 : 0;
     if ((unsigned long long)m > longest) longest = (unsigned long long)m;
   }
-  // longest column: one atomic per wave at most, and none once a longer
-  // column is known (atomics on one address queue)
+  if (!max_len) return;
+  // longest column: one atomic per workgroup (they queue on one address)
+  __shared__ unsigned long long wl[kBlock / kWave];
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) {
     const unsigned long long o = __shfl_xor(longest, off);
     longest = o > longest ? o : longest;
   }
-  if ((threadIdx.x & (kWave - 1)) == 0 &&
-      longest > __hip_atomic_load(max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+  if ((threadIdx.x & (kWave - 1)) == 0) wl[threadIdx.x / kWave] = longest;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kBlock / kWave; ++w) longest = wl[w] > longest ? wl[w] : longest;
     atomicMax(max_len, longest);
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void k_col_scatter(const int64_t *col_ptr, int64_t k,
@@ -472,13 +476,13 @@ static unsigned waves_grid(int64_t waves, unsigned cap = 8192) {
 }
 
 int launch_preprocess(const gencd_csc *X, int loss, int piece, int short_max, const Ws &w,
-                      hipStream_t s) {
+                      bool want_max, hipStream_t s) {
   (void)loss;
   const int64_t k = X->k;
   // counts: short -> tmp_cnt, long pieces -> tmp_cnt2, live flags -> col_of_pos (scratch)
   hipLaunchKernelGGL(k_col_counts, dim3(grid_for(k)), dim3(kBlock), 0, s, X->col_ptr, k, piece,
                      short_max, w.tmp_cnt, w.tmp_cnt2, w.col_of_pos,
-                     reinterpret_cast<unsigned long long *>(w.red) + 11);
+                     want_max ? reinterpret_cast<unsigned long long *>(w.red) + 11 : nullptr);
   int st = scan_exclusive(w.tmp_cnt, w.all_soff, k, w.scan_part, s);
   if (st) return st;
   st = scan_exclusive(w.tmp_cnt2, w.all_loff, k, w.scan_part, s);
@@ -573,8 +577,11 @@ __global__ __launch_bounds__(kBlock) void k_epoch_order(const int4 *live_rec, in
   }
 }
 
-__global__ void k_inc_epoch(int64_t *epoch) {
+__global__ void k_inc_epoch(int64_t *epoch, GridCtl *ctl) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *epoch += 1;
+  if (ctl && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < int(sizeof(GridCtl) / 4); i += int(blockDim.x))
+      reinterpret_cast<int32_t *>(ctl)[i] = 0;
 }
 
 // class counts for an explicit column list (step API and colour windows)
@@ -720,8 +727,8 @@ int launch_epoch_order(const Ws &w, int64_t k_live, int rule, uint64_t seed,
   return order_tail(w, k_live, nullptr, S, T, s, true);
 }
 
-int launch_inc_epoch(int64_t *epoch, hipStream_t s) {
-  hipLaunchKernelGGL(k_inc_epoch, dim3(1), dim3(64), 0, s, epoch);
+int launch_inc_epoch(int64_t *epoch, hipStream_t s, GridCtl *ctl) {
+  hipLaunchKernelGGL(k_inc_epoch, dim3(1), dim3(64), 0, s, epoch, ctl);
   return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
 }
 

@@ -29,6 +29,7 @@ struct IterArgs {
   int32_t improve;                 // extra quadratic-approximation steps per accepted proposal
   const int32_t *win_off;  // per-epoch window offsets, or null: [win_lo, win_hi)
   int32_t t, win_lo, win_hi;
+  int32_t S, k_live;       // whole-epoch kernels: window t is [t S, (t + 1) S) of k_live
   float *delta, *phi, *gacc, *gout, *wsnap;
   int32_t *acc;
   int32_t *bw_pos, *bw_phi;  // per-chunk winners of a two-stage global accept (scratch)
@@ -37,6 +38,22 @@ struct IterArgs {
   unsigned long long *scat;      // non-null: Update adds the nonzeros it scatters here
                                  // (replica line b % kChkRep of workgroup b, 16 words each)
 };
+
+// Control block of a grid of resident workgroups (gencd_grid.hip); all zero
+// before each launch.
+constexpr int kGridMax = 256;
+struct GridCtl {
+  int32_t count, members;
+  int32_t pad[30];
+  int32_t flag[kGridMax];
+};
+
+// One launch for all T windows of an epoch whose order is built (mode 0:
+// accept all, 1: Coloring; pieces of at most 64 * kUnroll entries, rows of at
+// most 2 GiB).  nnz: expected entries of a window.  A grid barrier that
+// runs out sets bit 16 of *bad.
+int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
+                      unsigned long long *bad, int64_t T, double nnz, hipStream_t s);
 
 // Whole epochs of a small accept-all problem in one workgroup
 // (gencd_solo.hip).
@@ -77,6 +94,8 @@ struct SoloPlan {
 // Shape for windows of S columns of a matrix whose longest column has
 // max_len entries (ok = false: the multi-workgroup kernels take it).
 SoloPlan solo_plan(int64_t n, int64_t nnz, int64_t k_live, int64_t max_len, int64_t S);
+// Rows that fit the LDS of one workgroup (a bound without the other sizes).
+constexpr int64_t kSoloMaxRows = 13312;
 int launch_solo(const SoloArgs &a, const SoloPlan &p, hipStream_t s);
 
 int fill_f32(float *p, int64_t m, float v, hipStream_t s);
@@ -87,8 +106,9 @@ int copy_i32(int32_t *d, const int32_t *src, int64_t m, hipStream_t s);
 
 int launch_validate(const gencd_csc *X, const float *y, int loss, bool matrix,
                     unsigned long long *bad, hipStream_t s);
+// want_max: leave the longest column's entries in word 11 of w.red.
 int launch_preprocess(const gencd_csc *X, int loss, int piece, int short_max, const Ws &w,
-                      hipStream_t s);
+                      bool want_max, hipStream_t s);
 int launch_curvature(const gencd_csc *X, int loss, int32_t n_short, int32_t n_lpieces,
                      const Ws &w, hipStream_t s);
 int launch_select_perm(int64_t m, uint64_t seed, int64_t epoch, int32_t *out, hipStream_t s);
@@ -98,7 +118,8 @@ int launch_select_perm(int64_t m, uint64_t seed, int64_t epoch, int32_t *out, hi
 int launch_epoch_order(const Ws &w, int64_t k_live, int rule, uint64_t seed,
                        const int64_t *epoch, int64_t num_colors, int64_t S, int64_t T,
                        hipStream_t s);
-int launch_inc_epoch(int64_t *epoch, hipStream_t s);
+// Epoch counter + 1; ctl (may be null): cleared for the next epoch's grid.
+int launch_inc_epoch(int64_t *epoch, hipStream_t s, GridCtl *ctl = nullptr);
 int launch_list_order(const Ws &w, const int32_t *J, int64_t nJ, hipStream_t s);
 // group: lanes per short column (4, 8, 16 or 32); short_bound / long_bound:
 // expected short columns / long pieces of a window (they size the grid; the

@@ -191,7 +191,7 @@ int64_t pstar_of(int64_t k_live, double rho) {
 
 int setup(const gencd_csc *X, const float *y, int loss, const gencd_params *p, void *ws_base,
           size_t ws_bytes, bool validate_matrix, hipStream_t s, Setup *out, int rho_iters,
-          bool need_y, int64_t nblocks, int block_iters) {
+          bool need_y, int64_t nblocks, int block_iters, bool want_max) {
   if (!csc_ok(X) || (need_y && !y)) return GENCD_ERR_INVALID_ARG;
   if (rho_iters < 0 || rho_iters > kRhoMaxIters) return GENCD_ERR_INVALID_ARG;
   if (nblocks < 0 || nblocks > kMaxBlocks || block_iters < 1 || block_iters > kBlockRhoMaxIters)
@@ -214,7 +214,7 @@ int setup(const gencd_csc *X, const float *y, int loss, const gencd_params *p, v
   if (st) return st;
   st = launch_validate(X, y, loss, validate_matrix, reinterpret_cast<unsigned long long *>(w.red) + 10, s);
   if (st) return st;
-  st = launch_preprocess(X, loss, out->piece, smax, w, s);
+  st = launch_preprocess(X, loss, out->piece, smax, w, want_max, s);
   if (st) return st;
   int32_t host[3] = {0, 0, 0};
   Red r{};
@@ -323,6 +323,7 @@ int run_check(const gencd_csc *X, const float *y, int loss, double lam, const fl
   int st = enqueue_check(X, y, loss, lam, w, su, resync, s, rep, &r);
   if (st) return st;
   GENCD_HIP(hipStreamSynchronize(s));
+  if (r.bad & 16ull) return GENCD_ERR_HIP;  // a grid barrier ran out: the state is not valid
   fold_check(rep, r, X->n, lam, out);
   return GENCD_OK;
 }
@@ -494,6 +495,14 @@ bool wants_rs(const gencd_params *p, int64_t positions, int64_t nnz, int64_t k_l
 // milliseconds, so that other streams' work is not held up for long).
 constexpr int64_t kSoloMaxWindows = 16384;
 
+// Windows for the resident grid: it is ahead of two launches per window up to
+// about 70k entries (61k 10.0 against 11.0 us, 80k 11.9 against 12.6, 122k
+// 15.0 against 12.7) and windows vary, so the line is drawn at 64k on average.
+constexpr double kGridWindowNnz = 65536.0;
+bool grid_fits(int64_t nnz, int64_t k_live, int64_t positions) {
+  return double(positions) * double(nnz) / double(k_live) <= kGridWindowNnz;
+}
+
 // Expected long pieces in a window of `positions` columns (sizes the grid;
 // the kernels stride over the actual count).
 int64_t long_bound_for(const Setup &su, int64_t positions) {
@@ -544,10 +553,10 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
   std::memset(st_out, 0, sizeof(*st_out));
   int st = params_ok(p, true);
   if (st) return st;
-  if (!w) return GENCD_ERR_INVALID_ARG;
+  if (!w || !csc_ok(X)) return GENCD_ERR_INVALID_ARG;
   Setup su;
   st = setup(X, y, p->loss, p, ws_base, ws_bytes, (p->flags & GENCD_VALIDATE_DEVICE) != 0, s, &su,
-             wants_rho(p) ? kRhoIters : 0, true, blocks_of(p));
+             wants_rho(p) ? kRhoIters : 0, true, blocks_of(p), kRhoIters, X->n <= kSoloMaxRows);
   if (st) return st;
   const Ws &ws = su.ws;
   const int rule = p->rule;
@@ -661,7 +670,20 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       !fused && !a.exact_accum && p->improve_steps == 0 && p->piece == 0 && p->group == 0 &&
       p->residual == 0;
   // a restart with half the window (divergence guard) keeps the choice
-  const bool solo = solo_rule && solo_plan(X->n, X->nnz, k_live, su.max_len, S).ok;
+  const bool solo = solo_rule && X->n <= kSoloMaxRows && solo_plan(X->n, X->nnz, k_live, su.max_len, S).ok;
+
+  // Mid-size windows: the windows of an epoch in one launch on a grid of
+  // resident workgroups.
+  const auto grid_ok = [&](int64_t positions) {
+    return mode != 2 && !solo && !prof && !fused && !a.exact_accum && p->improve_steps == 0 &&
+           su.piece <= kWave * kUnroll && X->n * 16 <= INT32_MAX && positions > 0 &&
+           !wants_rs(p, positions, X->nnz, k_live, X->n) && grid_fits(X->nnz, k_live, positions);
+  };
+  GridCtl *const gctl = reinterpret_cast<GridCtl *>(ws.scat);  // profiling counters otherwise
+  if (!prof) {
+    st = fill_i32(reinterpret_cast<int32_t *>(gctl), int64_t(sizeof(GridCtl) / 4), 0, s);
+    if (st) return st;
+  }
 
   // Enqueue one epoch: selection order (section 2.1), then every iteration
   // of Algorithm 1, then the epoch counter increment.  Every argument is
@@ -671,9 +693,21 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
                  ? launch_block_order(ws, k_live, p->seed, epoch_dev, T, es)
                  : launch_epoch_order(ws, k_live, rule, p->seed, epoch_dev, C, S, T, es);
     if (rc) return rc;
+    const int64_t mean_pos = T > 0 ? (k_live + T - 1) / T : 0;
+    const bool grid = T > 1 && grid_ok(mean_pos);
+    if (grid) {
+      a.win_off = (rule == GENCD_COLORING || rule == GENCD_BLOCK_SHOTGUN) ? ws.win_off : nullptr;
+      a.S = int32_t(S);
+      a.k_live = int32_t(k_live);
+      a.rs = nullptr;
+      rc = launch_epoch_grid(a, su.group, mode, gctl,
+                             reinterpret_cast<unsigned long long *>(ws.red) + 10, T,
+                             double(X->nnz) / double(T), es);
+      if (rc) return rc;
+    }
     PermKey cpk{};
     if (rule == GENCD_COLORING && !use_graph) cpk = make_perm_key(C, p->seed, e_host);
-    for (int64_t t = 0; t < T; ++t) {
+    for (int64_t t = 0; t < (grid ? 0 : T); ++t) {
       int64_t positions;
       if (rule == GENCD_COLORING) {
         a.win_off = ws.win_off;
@@ -719,7 +753,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       rc = launch_renorm(X->n, ws.zs, es);
       if (rc) return rc;
     }
-    return launch_inc_epoch(epoch_dev, es);
+    return launch_inc_epoch(epoch_dev, es, prof ? nullptr : gctl);
   };
 
   for (int64_t e = 0; status != GENCD_OK && e < p->max_epochs && k_live > 0; ++e) {

@@ -27,7 +27,7 @@ struct Setup {
   int piece = kDefaultPiece, group = kDefaultGroup;
   int32_t n_short = 0, n_lpieces = 0;
   int64_t k_live = 0;
-  int64_t max_len = 0;           // entries of the longest column
+  int64_t max_len = 0;           // entries of the longest column (want_max)
   std::vector<double> rho_hist;  // spectral-radius estimate after each power iteration
   double rho = 0.0;
   std::vector<double> brho;      // Block Shotgun: rho_b of every preset block
@@ -53,7 +53,7 @@ double bits_to_double(unsigned long long b);
 // false (no label check).
 int setup(const gencd_csc *X, const float *y, int loss, const gencd_params *p, void *ws_base,
           size_t ws_bytes, bool validate_matrix, hipStream_t s, Setup *out, int rho_iters = 0,
-          bool need_y = true, int64_t nblocks = 0, int block_iters = kRhoIters);
+          bool need_y = true, int64_t nblocks = 0, int block_iters = kRhoIters, bool want_max = false);
 
 // FP64 check of w (z64 = Xw, objective, KKT, duality gap; resync: the FP32
 // state from z64).  enqueue_check leaves the replica lines (kChkRep * 16
