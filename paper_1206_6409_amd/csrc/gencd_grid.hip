@@ -423,6 +423,306 @@ __global__ __launch_bounds__(kGridThreads) void k_epoch_grid(IterArgs a, GridCtl
   }
 }
 
+// A barrier at which a workgroup can leave a 16-bit mark for the others: the
+// flag is round << 16 | mark of its last marked window.  A member that is
+// already past this barrier shows the same mark until it passes the next
+// barrier, for which it needs this workgroup.  *seen: some member's mark is
+// `mark`.
+__device__ __forceinline__ bool grid_barrier_marked(GridCtl *c, unsigned long long *bad, int me,
+                                                    int members, uint32_t round, uint32_t own,
+                                                    uint32_t mark, int *sm, bool *seen) {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    if (threadIdx.x == 0) agent_store(&c->flag[me], int32_t(round << 16 | own));
+    int p = 0;
+    bool ok, hit;
+    do {
+      ok = true;
+      hit = false;
+      for (int i = int(threadIdx.x); i < members; i += kWave) {
+        const uint32_t f = uint32_t(agent_load(&c->flag[i]));
+        ok = ok && (f >> 16) >= round;
+        hit = hit || (f & 0xFFFFu) == mark;
+      }
+    } while (!__all(ok) && ++p < kGridPolls);
+    const bool any = __any(hit);
+    if (threadIdx.x == 0) {
+      sm[0] = p < kGridPolls;
+      sm[1] = any;
+      if (p >= kGridPolls) atomicOr(bad, 16ull);
+    }
+  }
+  __syncthreads();
+  *seen = sm[1] != 0;
+  return sm[0] != 0;
+}
+
+// Thread-Greedy (section 2.3): in each block of B window positions the first
+// one with the smallest phi is accepted.  Per window: Propose (increments and
+// proxies of short and one-piece columns, partial sums of split ones, as
+// agent-scope words) | barrier | one wave per block finishes the block's split
+// columns, finds the winner and scatters it | barrier.  A winner of more than
+// kDirect entries is published instead and scattered by all waves, piece by
+// chunk, before a third barrier that only such windows have (with a text-like
+// matrix most have one).  Bound by the three or two barriers and the chains
+// between them.  Per window of |J| = 1024, B = 64, 14k entries: three launches
+// 17 us, this 12.
+constexpr int32_t kDirect = kWave * kUnroll;
+
+// One window position as its block's accept sees it.
+struct AcceptPos {
+  int4 ds;          // short descriptor (length 0: long column)
+  int32_t pf, pe;   // pieces of a long column
+  float c, w;
+};
+constexpr int kSplits = 4;
+
+template <int GS>
+__global__ __launch_bounds__(kGridThreads) void k_greedy_grid(IterArgs a, GridCtl *ctl,
+                                                               unsigned long long *bad, int32_t T,
+                                                               int32_t B) {
+  __shared__ int sm[2];
+  __shared__ int smb[2];
+  int members;
+  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(ctl, sm, members));
+  members = __builtin_amdgcn_readfirstlane(members);
+  if (me < 0) return;
+  const int lane = int(threadIdx.x) & (kWave - 1);
+  const int slot = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+  GridWave<GS> gw{a, slot * members + me, members * (kGridThreads / kWave), lane, 0, 0, 0};
+  gw.bounds(0, T);
+  const Rows z{__builtin_amdgcn_make_buffer_rsrc(a.zs, 0, int(a.nrows * 16), 0x00027000)};
+  // {phi, delta} of a window slot in one word (delta and phi are adjacent
+  // arrays of k); the published winners {first entry, length}, {0, delta} in the
+  // count scratch (two words a block of at least two positions)
+  unsigned long long *const prop = reinterpret_cast<unsigned long long *>(a.delta);
+  unsigned long long *const win = reinterpret_cast<unsigned long long *>(a.bw_pos);
+  auto word = [](uint32_t hi, float d) {
+    return static_cast<unsigned long long>(hi) << 32 | __float_as_uint(d);
+  };
+  WindowPos wp = gw.window(0, T), wn = gw.window(1, T);
+  Unit cur, nxt;
+  cur.d = gw.wave < gw.units(wp) ? gw.desc(wp, gw.wave) : make_int4(0, 0, 0, 0);
+  nxt.d = gw.wave < gw.units(wn) ? gw.desc(wn, gw.wave) : make_int4(0, 0, 0, 0);
+  gw.fill(gw.is_long(wp, gw.wave), cur);
+  unsigned long long acc_nnz = 0, acc_cnt = 0;  // this wave's accepted columns (lane 0)
+  uint32_t round = 0, own = 0;
+  __shared__ uint32_t published;  // this workgroup's last window with a published winner
+  if (threadIdx.x == 0) published = 0;
+  __syncthreads();
+  auto propose = [&](const Unit &x, int32_t u, const float4 (&r)[kUnroll]) {
+    const bool lng = gw.is_long(wp, u);
+    float s = 0.0f;
+#pragma unroll
+    for (int v = 0; v < kUnroll; ++v)
+      if (gw.has(lng, x, v)) s += x.vv[v] * dloss_f32(a.loss, r[v].z, r[v].x + r[v].y);
+    s = unit_sum<GS>(lng, s);
+    if (lng && x.d.w >= 0) {
+      if (lane == 0) agent_store(&a.gacc[wp.q0 + u], s);
+    } else if ((x.d.w & 0x7FFFFFFF) > 0) {
+      float d, ph;
+      propose_f32(s / a.n_f, x.c, x.w, a.lam, d, ph);
+      if ((lng ? lane : (lane & (GS - 1))) == 0)
+        agent_store(&prop[x.d.z - wp.P0], word(__float_as_uint(ph), d));
+    }
+  };
+  // what an accept reads of a position that no wave writes, in two stages
+  auto accept_desc = [&](int32_t q, AcceptPos &x) {
+    x.ds = a.desc_s[q];
+    x.pf = a.loff[q];
+    x.pe = a.loff[q + 1];
+  };
+  auto accept_scalars = [&](AcceptPos &x) {
+    x.c = a.c[x.ds.y];
+    x.w = a.w[x.ds.y];
+  };
+  // position of this lane in the wave's first block of a window
+  auto accept_pos = [&](const WindowPos &w) {
+    const int32_t lo = w.P0 + gw.wave * B, p = lo + lane;
+    return lane < B && p < w.P1 ? p : (lo < w.P1 ? lo : w.P0);
+  };
+  AcceptPos at{}, atn{};
+  accept_desc(accept_pos(wp), at);
+  for (int32_t t = 0; t < T; ++t) {
+    const WindowPos w2 = gw.window(t + 2, T);
+    const int32_t nu = gw.units(wp);
+    const uint32_t mark = uint32_t(t + 1) & 0xFFFFu;
+    float4 r[kUnroll];
+    if (gw.wave < nu) {
+#pragma unroll
+      for (int v = 0; v < kUnroll; ++v) r[v] = row_load(z, cur.ri[v]);
+    }
+    if (gw.wave < gw.units(wn)) gw.fill(gw.is_long(wn, gw.wave), nxt);
+    const int4 dd = gw.wave < gw.units(w2) ? gw.desc(w2, gw.wave) : make_int4(0, 0, 0, 0);
+    const int32_t m = wp.P1 - wp.P0, nblk = (m + B - 1) / B;
+    if (gw.wave < nblk) accept_scalars(at);
+    if (t + 1 < T) accept_desc(accept_pos(wn), atn);
+    if (gw.wave < nu) propose(cur, gw.wave, r);
+    for (int32_t u = gw.wave + gw.nw; u < nu; u += gw.nw) {
+      Unit x;
+      x.d = gw.desc(wp, u);
+      gw.fill(gw.is_long(wp, u), x);
+#pragma unroll
+      for (int v = 0; v < kUnroll; ++v) r[v] = row_load(z, x.ri[v]);
+      propose(x, u, r);
+    }
+    bool unused;
+    if (!grid_barrier_marked(ctl, bad, me, members, ++round, own, ~0u, smb, &unused)) return;
+    // Accept and scatter
+    for (int32_t b = gw.wave; b < nblk; b += gw.nw) {
+      const int32_t lo = wp.P0 + b * B, hi = lo + B < wp.P1 ? lo + B : wp.P1;
+      float best = INFINITY, bd = 0.0f;
+      int32_t bpos = INT32_MAX;
+      int4 bds = make_int4(0, 0, 0, 0);
+      for (int32_t c0 = lo; c0 < hi; c0 += kWave) {
+        const int32_t p = c0 + lane;
+        const bool ok = p < hi;
+        if (b != gw.wave || c0 != lo) {
+          accept_desc(ok ? p : lo, at);
+          accept_scalars(at);
+        }
+        const int4 ds = at.ds;
+        const unsigned long long v = agent_load(&prop[(ok ? p : lo) - wp.P0]);
+        float ph = __uint_as_float(uint32_t(v >> 32)), d = __uint_as_float(uint32_t(v));
+        unsigned long long left = __ballot(ok && at.pe - at.pf > 1);
+        while (left) {  // split columns of the block, kSplits of them at once
+          int g[kSplits];
+          float part[kSplits];
+#pragma unroll
+          for (int i = 0; i < kSplits; ++i) {
+            g[i] = left ? __builtin_ctzll(left) : -1;
+            left &= left - 1;  // 0 stays 0
+            part[i] = 0.0f;
+            if (g[i] < 0) continue;
+            const int32_t f = __builtin_amdgcn_readlane(at.pf, g[i]);
+            const int32_t np = __builtin_amdgcn_readlane(at.pe, g[i]) - f;
+            if (lane < np) part[i] = agent_load(&a.gacc[f + lane]);
+            for (int32_t q = lane + kWave; q < np; q += kWave) part[i] += agent_load(&a.gacc[f + q]);
+          }
+#pragma unroll
+          for (int i = 0; i < kSplits; ++i) {
+            if (g[i] < 0) break;
+            const float grad = rows_sum(row_group_sum<16>(part[i])) / a.n_f;
+            float de, pp;
+            propose_f32(grad, at.c, at.w, a.lam, de, pp);  // lane g[i]'s is the column's
+            if (lane == g[i]) {
+              ph = pp;
+              d = de;
+            }
+          }
+        }
+        if (ok && ph < best) {  // a lane's positions come in increasing order
+          best = ph;
+          bpos = p;
+          bd = d;
+          bds = ds;
+        }
+      }
+      float wb = best;
+      int32_t wpos = bpos;
+#pragma unroll
+      for (int off = kWave / 2; off > 0; off >>= 1) {
+        const float ob = __shfl_xor(wb, off);
+        const int32_t op = __shfl_xor(wpos, off);
+        if (ob < wb || (ob == wb && op < wpos)) {
+          wb = ob;
+          wpos = op;
+        }
+      }
+      uint32_t pub_beg = 0, pub_len = 0;
+      float d = 0.0f;
+      if (wpos != INT32_MAX) {  // uniform: every lane holds the winner
+        const int g = __builtin_ctzll(__ballot(bpos == wpos));
+        d = __shfl(bd, g);
+        const int32_t j = __shfl(bds.y, g), len0 = __shfl(bds.w, g) & 0x7FFFFFFF;
+        uint32_t beg = uint32_t(__shfl(bds.x, g));
+        int32_t len = len0;
+        if (len0 == 0) {  // a long column
+          const int64_t cb = a.col_ptr[j];
+          beg = uint32_t(cb);
+          len = int32_t(a.col_ptr[j + 1] - cb);
+        }
+        if (lane == 0) {
+          acc_nnz += (unsigned long long)len;
+          acc_cnt += 1ull;
+          if (d != 0.0f) a.w[j] += d;
+        }
+        if (d != 0.0f && len > kDirect) {
+          pub_beg = beg;
+          pub_len = uint32_t(len);
+          if (lane == 0) published = mark;
+        } else if (d != 0.0f) {
+          int32_t ri[kUnroll];
+          float vv[kUnroll];
+#pragma unroll
+          for (int v = 0; v < kUnroll; ++v) {
+            const int32_t e = v * kWave + lane;
+            const int64_t from = int64_t(beg) + (e < len ? e : 0);
+            ri[v] = a.row_idx[from];
+            vv[v] = a.val[from];
+          }
+#pragma unroll
+          for (int v = 0; v < kUnroll; ++v)
+            if (v * kWave + lane < len) atomicAdd(&a.zs[ri[v]].y, d * vv[v]);
+        }
+      }
+      if (lane == 0) {
+        agent_store(&win[2 * b], static_cast<unsigned long long>(pub_beg) << 32 | pub_len);
+        agent_store(&win[2 * b + 1], word(0u, d));
+      }
+    }
+    __syncthreads();
+    own = published;
+    bool spread = false;
+    if (!grid_barrier_marked(ctl, bad, me, members, ++round, own, mark, smb, &spread)) return;
+    if (spread) {  // the same decision in every workgroup
+      int32_t seen = 0;  // chunks handed out so far
+      for (int32_t b0 = 0; b0 < nblk; b0 += kWave) {
+        const int32_t b = b0 + lane < nblk ? b0 + lane : b0;
+        unsigned long long v = agent_load(&win[2 * b]);
+        const unsigned long long dv = agent_load(&win[2 * b + 1]);
+        if (b0 + lane >= nblk) v = 0;
+        unsigned long long left = __ballot(uint32_t(v) != 0);
+        while (left) {
+          const int g = __builtin_ctzll(left);
+          left &= left - 1;
+          const uint32_t beg = uint32_t(__builtin_amdgcn_readlane(int(v >> 32), g));
+          const int32_t len = __builtin_amdgcn_readlane(int(v), g);
+          const float d = __int_as_float(__builtin_amdgcn_readlane(int(dv), g));
+          const int32_t nc = (len + kDirect - 1) / kDirect;
+          int32_t c = (gw.wave - seen) % gw.nw;
+          for (c += c < 0 ? gw.nw : 0; c < nc; c += gw.nw) {
+            int32_t ri[kUnroll];
+            float vv[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+              const int32_t e = c * kDirect + u * kWave + lane;
+              const int64_t from = int64_t(beg) + (e < len ? e : 0);
+              ri[u] = a.row_idx[from];
+              vv[u] = a.val[from];
+            }
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u)
+              if (c * kDirect + u * kWave + lane < len) atomicAdd(&a.zs[ri[u]].y, d * vv[u]);
+          }
+          seen = (seen + nc) % gw.nw;
+        }
+      }
+      if (!grid_barrier_marked(ctl, bad, me, members, ++round, own, ~0u, smb, &unused)) return;
+    }
+    wp = wn;
+    wn = w2;
+    cur = nxt;
+    nxt.d = dd;
+    at = atn;
+  }
+  if (lane == 0 && acc_cnt > 0) {
+    atomicAdd(a.counters + 0, acc_nnz);
+    atomicAdd(a.counters + 1, acc_cnt);
+  }
+}
+
 // Workgroups for windows of `nnz` entries on average.  A barrier takes 0.9 us
 // among 32, 1.2 among 64 and 1.8 among 128 (every member reads every flag);
 // more of them gather and scatter faster.  Per window, 32 / 64 / 128: 2k
@@ -440,10 +740,25 @@ static void launch_grid_g(const IterArgs &a, int mode, GridCtl *ctl, unsigned lo
 }
 
 int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
-                      unsigned long long *bad, int64_t T, double nnz, hipStream_t s) {
+                      unsigned long long *bad, int64_t T, double nnz, int64_t block, hipStream_t s) {
+  if (mode == 2 && (T > kGreedyMaxT || block < 2 || block > kGreedyMaxBlock))
+    return GENCD_ERR_INVALID_ARG;
   if (a.piece > kWave * kUnroll || T < 1 || a.k_live < 1 || a.nrows * 16 > INT32_MAX)
     return GENCD_ERR_INVALID_ARG;
   const unsigned m = grid_size(nnz);
+  if (mode == 2) {
+    const auto tg = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, int32_t(T),
+                         int32_t(block));
+    };
+    switch (group) {
+      case 4: tg(k_greedy_grid<4>); break;
+      case 8: tg(k_greedy_grid<8>); break;
+      case 16: tg(k_greedy_grid<16>); break;
+      default: tg(k_greedy_grid<32>); break;
+    }
+    return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
+  }
   switch (group) {
     case 4: launch_grid_g<4>(a, mode, ctl, bad, int32_t(T), m, s); break;
     case 8: launch_grid_g<8>(a, mode, ctl, bad, int32_t(T), m, s); break;

@@ -42,6 +42,10 @@ struct IterArgs {
 // Control block of a grid of resident workgroups (gencd_grid.hip); all zero
 // before each launch.
 constexpr int kGridMax = 256;
+// Thread-Greedy on the grid: three barriers a window at most, counted in 16
+// bits; one wave walks a block, 64 positions a round.
+constexpr int64_t kGreedyMaxT = 21000;
+constexpr int64_t kGreedyMaxBlock = 256;
 struct GridCtl {
   int32_t count, members;
   int32_t pad[30];
@@ -49,11 +53,13 @@ struct GridCtl {
 };
 
 // One launch for all T windows of an epoch whose order is built (mode 0:
-// accept all, 1: Coloring; pieces of at most 64 * kUnroll entries, rows of at
+// accept all, 1: Coloring, 2: Thread-Greedy with 2 to kGreedyMaxBlock
+// positions per block and at most kGreedyMaxT windows; pieces of at most 64 * kUnroll entries, rows of at
 // most 2 GiB).  nnz: expected entries of a window.  A grid barrier that
 // runs out sets bit 16 of *bad.
 int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
-                      unsigned long long *bad, int64_t T, double nnz, hipStream_t s);
+                      unsigned long long *bad, int64_t T, double nnz, int64_t block,
+                      hipStream_t s);
 
 // Whole epochs of a small accept-all problem in one workgroup
 // (gencd_solo.hip).

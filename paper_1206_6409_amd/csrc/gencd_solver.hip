@@ -498,9 +498,14 @@ constexpr int64_t kSoloMaxWindows = 16384;
 // Windows for the resident grid: it is ahead of two launches per window up to
 // about 70k entries (61k 10.0 against 11.0 us, 80k 11.9 against 12.6, 122k
 // 15.0 against 12.7) and windows vary, so the line is drawn at 64k on average.
+// Thread-Greedy replaces three launches, but a wave per block finishes and
+// scatters alone: ahead up to about 40k entries (15k 11.4 against 15.6 us, 56k
+// 18.6 against 18.0).
 constexpr double kGridWindowNnz = 65536.0;
-bool grid_fits(int64_t nnz, int64_t k_live, int64_t positions) {
-  return double(positions) * double(nnz) / double(k_live) <= kGridWindowNnz;
+constexpr double kGridGreedyNnz = 32768.0;
+bool grid_fits(int64_t nnz, int64_t k_live, int64_t positions, bool greedy) {
+  return double(positions) * double(nnz) / double(k_live) <=
+         (greedy ? kGridGreedyNnz : kGridWindowNnz);
 }
 
 // Expected long pieces in a window of `positions` columns (sizes the grid;
@@ -675,9 +680,12 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
   // Mid-size windows: the windows of an epoch in one launch on a grid of
   // resident workgroups.
   const auto grid_ok = [&](int64_t positions) {
-    return mode != 2 && !solo && !prof && !fused && !a.exact_accum && p->improve_steps == 0 &&
+    const bool accept = mode != 2 || (rule == GENCD_THREAD_GREEDY && p->block >= 2 &&
+                                      p->block <= kGreedyMaxBlock &&
+                                      k_live <= kGreedyMaxT * S);
+    return accept && !solo && !prof && !fused && !a.exact_accum && p->improve_steps == 0 &&
            su.piece <= kWave * kUnroll && X->n * 16 <= INT32_MAX && positions > 0 &&
-           !wants_rs(p, positions, X->nnz, k_live, X->n) && grid_fits(X->nnz, k_live, positions);
+           !wants_rs(p, positions, X->nnz, k_live, X->n) && grid_fits(X->nnz, k_live, positions, mode == 2);
   };
   GridCtl *const gctl = reinterpret_cast<GridCtl *>(ws.scat);  // profiling counters otherwise
   if (!prof) {
@@ -702,7 +710,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       a.rs = nullptr;
       rc = launch_epoch_grid(a, su.group, mode, gctl,
                              reinterpret_cast<unsigned long long *>(ws.red) + 10, T,
-                             double(X->nnz) / double(T), es);
+                             double(X->nnz) / double(T), p->block, es);
       if (rc) return rc;
     }
     PermKey cpk{};

@@ -89,3 +89,29 @@ def test_concurrent_solves_on_two_streams():
         t.join()
     for i in range(2):
         assert _rel(got[i].astype(np.float64), want[i].astype(np.float64)) <= 1e-5
+
+
+# blocks of one to several rounds of a wave, ragged last blocks and windows,
+# winners that one wave scatters and winners spread over the grid (columns of
+# more than 1024 entries win their blocks), graph replays
+@pytest.mark.parametrize("scale,S,B,group,piece,flags", [
+    (0.05, 1024, 64, 8, 256, 0),
+    (0.05, 1000, 100, 4, 64, G.USE_GRAPH),
+    (0.05, 333, 2, 16, 128, 0),
+    (0.05, 4097, 256, 32, 256, 0),
+    (0.2, 512, 32, 8, 256, G.USE_GRAPH),
+])
+def test_thread_greedy_matches_the_separate_launches(scale, S, B, group, piece, flags):
+    """GENCD_PROFILE keeps one launch per phase; the picks of two epochs are
+    the same and the weights differ by FP32 rounding."""
+    P = synth.c2_zipf_logistic(scale=scale)
+    X, y = G.Matrix.of(P), torch.as_tensor(P.y, device="cuda")
+    lam = 0.05 * G.lambda_max(X, y, P.loss)
+    kw = dict(rule=G.THREAD_GREEDY, select_size=S, block=B, seed=3, tol=0.0, max_epochs=2,
+              group=group, piece=piece)
+    a = G.solve(X, y, G.make_params(P.loss, lam, flags=flags, **kw))
+    b = G.solve(X, y, G.make_params(P.loss, lam, flags=G.PROFILE, **kw))
+    for key in ("iters", "coord_updates", "nnz_updates"):
+        assert a.stats[key] == b.stats[key], key
+    assert _rel(a.w.cpu().numpy().astype(np.float64), b.w.cpu().numpy().astype(np.float64)) <= 1e-5
+    assert _rel(a.z.cpu().numpy().astype(np.float64), b.z.cpu().numpy().astype(np.float64)) <= 1e-5
