@@ -20,10 +20,10 @@
 // single-column rounds) spreads its row prefixes over the whole grid, into
 // a bitmap per frontier column in global memory; a large one takes one
 // workgroup per column with the bitmap in LDS.
+#include <cstddef>
 #include <vector>
 
-#include "gencd_common.hpp"
-#include "gencd_kernels.hpp"
+#include "gencd_gridsync.hpp"
 
 namespace gencd {
 
@@ -40,9 +40,9 @@ struct ColorWs {
   int32_t *order;             // [k] column at each priority rank
   int32_t *rank;              // [k] priority rank of each column
   int32_t *roff;              // [k+1] first slot of each rank's entries in the rank-ordered list
-  int32_t *erank;             // [nnz] priority rank of the column of each CSC entry
+  int32_t *ecol;              // [nnz] column of each CSC entry
   int32_t *row_ptr;           // [n+1]
-  int32_t *rank_at;           // [nnz] CSR slot -> column rank
+  int32_t *col_at;            // [nnz] CSR slot -> column
   int32_t *pos_in_row;        // [nnz] CSC entry -> position in its CSR row
   int32_t *count;             // [k]
   int32_t *front_a, *front_b; // [k]
@@ -75,9 +75,9 @@ static size_t color_layout(int64_t n, int64_t k, int64_t nnz, void *base, ColorW
   c.order = static_cast<int32_t *>(take(sizeof(int32_t) * k));
   c.rank = static_cast<int32_t *>(take(sizeof(int32_t) * k));
   c.roff = static_cast<int32_t *>(take(sizeof(int32_t) * (k + 1)));
-  c.erank = static_cast<int32_t *>(take(sizeof(int32_t) * nnz));
+  c.ecol = static_cast<int32_t *>(take(sizeof(int32_t) * nnz));
   c.row_ptr = static_cast<int32_t *>(take(sizeof(int32_t) * (n + 1)));
-  c.rank_at = static_cast<int32_t *>(take(sizeof(int32_t) * nnz));
+  c.col_at = static_cast<int32_t *>(take(sizeof(int32_t) * nnz));
   c.pos_in_row = static_cast<int32_t *>(take(sizeof(int32_t) * nnz));
   c.count = static_cast<int32_t *>(take(sizeof(int32_t) * k));
   c.front_a = static_cast<int32_t *>(take(sizeof(int32_t) * k));
@@ -120,14 +120,19 @@ __global__ __launch_bounds__(kBlock) void k_rank_of(const int32_t *order, int64_
   }
 }
 
+// Loads a wave keeps in flight along a column, here and in k_init_count: the
+// heaviest column's walk is the kernel's length (1.26 -> 0.36 and
+// 0.85 -> 0.29 ms on the Lasso workload).
+constexpr int kListDeep = 8;
+
 // One wave per rank: the CSC entries listed column by column in priority
-// order (sort key: the entry's row, value: the entry), the rank of every
-// entry's column, and the row histogram.  A stable sort of this list by row
+// order (sort key: the entry's row, value: the entry), the column of every
+// entry, and the row histogram.  A stable sort of this list by row
 // leaves each row's entries in priority order.
 __global__ __launch_bounds__(kBlock) void k_csr_list(const int64_t *col_ptr, const int32_t *row_idx,
                                                       int64_t k, const int32_t *order,
                                                       const int32_t *roff, uint32_t *keys,
-                                                      int32_t *vals, int32_t *erank, int32_t *hist) {
+                                                      int32_t *vals, int32_t *ecol, int32_t *hist) {
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t wid = (int64_t(blockIdx.x) * kBlock + threadIdx.x) / kWave;
   const int64_t nw = int64_t(gridDim.x) * kBlock / kWave;
@@ -135,25 +140,33 @@ __global__ __launch_bounds__(kBlock) void k_csr_list(const int64_t *col_ptr, con
     const int32_t j = order[r];
     const int64_t e0 = col_ptr[j], e1 = col_ptr[j + 1];
     const int64_t p0 = roff[r];
-    for (int64_t e = e0 + lane; e < e1; e += kWave) {
-      const int32_t row = row_idx[e];
-      keys[p0 + (e - e0)] = uint32_t(row);
-      vals[p0 + (e - e0)] = int32_t(e);
-      erank[e] = int32_t(r);
+    int64_t e = e0 + lane;
+    auto put = [&](int64_t at, int32_t row) {
+      keys[p0 + (at - e0)] = uint32_t(row);
+      vals[p0 + (at - e0)] = int32_t(at);
+      ecol[at] = j;
       atomicAdd(&hist[row], 1);
+    };
+    for (; e + (kListDeep - 1) * kWave < e1; e += kListDeep * kWave) {
+      int32_t row[kListDeep];
+#pragma unroll
+      for (int u = 0; u < kListDeep; ++u) row[u] = row_idx[e + u * kWave];
+#pragma unroll
+      for (int u = 0; u < kListDeep; ++u) put(e + u * kWave, row[u]);
     }
+    for (; e < e1; e += kWave) put(e, row_idx[e]);
   }
 }
 
 __global__ __launch_bounds__(kBlock) void k_csr_fill(const uint32_t *rows, const int32_t *ents,
                                                       int64_t nnz, const int32_t *row_ptr,
-                                                      const int32_t *erank, int32_t *rank_at,
+                                                      const int32_t *ecol, int32_t *col_at,
                                                       int32_t *pos_in_row) {
   for (int64_t q = int64_t(blockIdx.x) * kBlock + threadIdx.x; q < nnz;
        q += int64_t(gridDim.x) * kBlock) {
     const int32_t row = int32_t(rows[q]);
     const int32_t e = ents[q];
-    rank_at[q] = erank[e];
+    col_at[q] = ecol[e];
     pos_in_row[e] = int32_t(q) - row_ptr[row];
   }
 }
@@ -176,7 +189,12 @@ __global__ __launch_bounds__(kBlock) void k_init_count(const int64_t *col_ptr, i
   for (int64_t j = wid; j < k; j += nw) {
     const int64_t e0 = col_ptr[j], e1 = col_ptr[j + 1];
     int32_t s = 0;
-    for (int64_t e = e0 + lane; e < e1; e += kWave) s += pos_in_row[e];
+    int64_t e = e0 + lane;
+    for (; e + (kListDeep - 1) * kWave < e1; e += kListDeep * kWave) {
+#pragma unroll
+      for (int u = 0; u < kListDeep; ++u) s += pos_in_row[e + u * kWave];
+    }
+    for (; e < e1; e += kWave) s += pos_in_row[e];
     s = group_sum<kWave>(s);
     if (lane == 0) {
       count[j] = s;
@@ -200,9 +218,8 @@ __global__ __launch_bounds__(kBlock) void k_init_count(const int64_t *col_ptr, i
 // (one workgroup per frontier column, LDS bitmap of the colours so far)
 __device__ void mex_blocks(int64_t vb, int64_t nvb, uint32_t *bits, int32_t &best,
                            const int32_t *Fp, const int64_t *col_ptr, const int32_t *row_idx,
-                           const int32_t *front, const int32_t *row_ptr, const int32_t *rank_at,
-                           const int32_t *pos_in_row, const int32_t *order, int32_t *color,
-                           int32_t *ctl) {
+                           const int32_t *front, const int32_t *row_ptr, const int32_t *col_at,
+                           const int32_t *pos_in_row, int32_t *color, int32_t *ctl) {
   const int32_t F = *Fp;
   if (F <= kFlatMax) return;  // k_mex_flat / k_mex_pick take small frontiers
   const int32_t maxc = ctl[1];  // largest colour so far (-1 initially)
@@ -218,7 +235,7 @@ __device__ void mex_blocks(int64_t vb, int64_t nvb, uint32_t *bits, int32_t &bes
       const int32_t r = row_idx[e];
       const int32_t a = row_ptr[r], b = a + pos_in_row[e];
       for (int32_t q = a + l; q < b; q += kSG) {
-        const int32_t c = color[order[rank_at[q]]];
+        const int32_t c = color[col_at[q]];
         if (c >= 0 && c < kMexWords * 32) atomicOr(&bits[c >> 5], 1u << (c & 31));
       }
     }
@@ -255,8 +272,8 @@ __device__ void mex_blocks(int64_t vb, int64_t nvb, uint32_t *bits, int32_t &bes
 __device__ void mex_flat_blocks(int64_t vb, int64_t nvb, uint32_t *bits, const int32_t *Fp,
                                 const int32_t *foff, const int32_t *front, const int64_t *col_ptr,
                                 const int32_t *row_idx, const int32_t *row_ptr,
-                                const int32_t *rank_at, const int32_t *pos_in_row,
-                                const int32_t *order, const int32_t *color, const int32_t *ctl,
+                                const int32_t *col_at, const int32_t *pos_in_row,
+                                const int32_t *color, const int32_t *ctl,
                                 uint32_t *gbits) {
   const int32_t F = *Fp;
   if (F > kFlatMax || F == 0) return;
@@ -284,7 +301,7 @@ __device__ void mex_flat_blocks(int64_t vb, int64_t nvb, uint32_t *bits, const i
       const int32_t r = row_idx[e];
       const int32_t a = row_ptr[r], b = a + pos_in_row[e];
       for (int32_t q = a + l; q < b; q += kSG) {
-        const int32_t c = color[order[rank_at[q]]];
+        const int32_t c = color[col_at[q]];
         if (c >= 0 && c < words * 32) atomicOr(&bits[c >> 5], 1u << (c & 31));
       }
     }
@@ -446,8 +463,7 @@ constexpr int kProbe = 8;
 __device__ void decrement_blocks(int64_t vb, int64_t nvb, int32_t *hkey, int32_t *hcnt,
                                  const int32_t *Fp, const int64_t *col_ptr, const int32_t *row_idx,
                                  const int32_t *front, const int32_t *foff, const int32_t *row_ptr,
-                                 const int32_t *rank_at, const int32_t *pos_in_row,
-                                 const int32_t *order, int32_t *count, int32_t *next,
+                                 const int32_t *col_at, const int32_t *pos_in_row, int32_t *count, int32_t *next,
                                  int32_t *next_cnt) {
   const int32_t F = *Fp;
   const int32_t total = foff[F];
@@ -470,7 +486,7 @@ __device__ void decrement_blocks(int64_t vb, int64_t nvb, int32_t *hkey, int32_t
     const int32_t r = row_idx[e];
     const int32_t b = row_ptr[r + 1];
     for (int32_t q = row_ptr[r] + pos_in_row[e] + 1 + l; q < b; q += kSG) {
-      const int32_t j2 = order[rank_at[q]];
+      const int32_t j2 = col_at[q];
       uint32_t h = (uint32_t(j2) * 2654435761u) & (kHash - 1);
       bool done = false;
       for (int p = 0; p < kProbe && !done; ++p, h = (h + 1) & (kHash - 1)) {
@@ -501,27 +517,346 @@ __device__ void decrement_blocks(int64_t vb, int64_t nvb, int32_t *hkey, int32_t
 // depend on each other.  The LDS buffer serves the role a workgroup takes.
 __global__ __launch_bounds__(kBlock) void k_round_work(
     const int32_t *Fp, const int64_t *col_ptr, const int32_t *row_idx, const int32_t *front,
-    const int32_t *foff, const int32_t *row_ptr, const int32_t *rank_at, const int32_t *pos_in_row,
-    const int32_t *order, int32_t *color, int32_t *ctl, uint32_t *gbits, int32_t *count,
+    const int32_t *foff, const int32_t *row_ptr, const int32_t *col_at, const int32_t *pos_in_row,
+    int32_t *color, int32_t *ctl, uint32_t *gbits, int32_t *count,
     int32_t *next, int32_t *next_cnt, int32_t gm, int32_t gf) {
   __shared__ uint32_t lds[kMexWords];  // mex bitmap, or the decrement hash (2 x kHash ints)
   __shared__ int32_t best;
   static_assert(2 * kHash <= kMexWords, "hash table fits the bitmap buffer");
   const int64_t b = blockIdx.x;
   if (b < gm) {
-    mex_blocks(b, gm, lds, best, Fp, col_ptr, row_idx, front, row_ptr, rank_at, pos_in_row,
-               order, color, ctl);
+    mex_blocks(b, gm, lds, best, Fp, col_ptr, row_idx, front, row_ptr, col_at, pos_in_row,
+               color, ctl);
   } else if (b < gm + gf) {
-    mex_flat_blocks(b - gm, gf, lds, Fp, foff, front, col_ptr, row_idx, row_ptr, rank_at,
-                    pos_in_row, order, color, ctl, gbits);
+    mex_flat_blocks(b - gm, gf, lds, Fp, foff, front, col_ptr, row_idx, row_ptr, col_at,
+                    pos_in_row, color, ctl, gbits);
   } else {
     int32_t *h = reinterpret_cast<int32_t *>(lds);
     decrement_blocks(b - gm - gf, int64_t(gridDim.x) - gm - gf, h, h + kHash, Fp, col_ptr,
-                     row_idx, front, foff, row_ptr, rank_at, pos_in_row, order, count, next,
+                     row_idx, front, foff, row_ptr, col_at, pos_in_row, count, next,
                      next_cnt);
   }
 }
 
+
+// ---------------------------------------------------------------------------
+// The rounds on a resident grid (gencd_gridsync.hpp): a round is a few
+// microseconds of dependent loads, and on the Lasso workload (200k x
+// 1M, about 30 entries a row) there are 1824 of them, so five launches a round (27 us) were
+// almost all of the colouring.  Here a launch runs up to kCgRounds of them, with
+// one barrier a round.  Waves take frontier columns (columns of more than
+// kCgChunk entries in chunks, any wave), mark the colours of the earlier columns
+// of each entry's row and count the later ones down, in one walk over the row; a
+// whole column's wave then has its mex, chunks OR their bitmaps into the
+// column's global one, and the last of them (a ticket per column) takes the mex
+// from there.  Colours, lists, counters and bitmaps are agent-scope words; the
+// CSR arrays are only read.  A round is 15.5 us (whole call 53 -> 29.8 ms): the
+// chain list -> entry -> row -> colours -> LDS counts (5 us), the bitmap's and
+// the ticket's round trips, the counters' atomics, the lists' and the barrier.
+// ---------------------------------------------------------------------------
+constexpr int kCgThreads = 1024;
+constexpr int kCgWaves = kCgThreads / kWave;
+constexpr int kCgGrid = 64;        // workgroups (32: 36.7 ms, 64: 33.0, 128: 33.2)
+constexpr int kCgWords = 256;      // bitmap words: up to 8192 colours
+constexpr int32_t kCgChunk = 16;   // entries of a chunk (64: 48 ms, 32: 36.0, 16: 32.4, 8: 35.4)
+constexpr int kCgCut = 1536;       // cut columns a round can hold
+constexpr int32_t kCgRounds = 4096;
+constexpr int kCgSG = 16;          // lanes per entry
+constexpr int kCgPer = kWave / kCgSG;  // entries a wave walks at once ...
+constexpr int kCgDeep = 4;         // ... times this many groups of loads in flight
+static_assert(kCgChunk % (kCgPer * kCgDeep) == 0, "whole groups per chunk");
+
+// Control block, at the end of gbits (the bitmaps of cut columns take the
+// first kCgCut * kCgWords words).
+struct ColorCtl {
+  GridCtl g;
+  unsigned long long bad;
+  int32_t whole[3], cut[3];        // frontier sizes by round modulo 3
+  int32_t max_color, colored, round, status;  // status 0: rounds left, 1: done,
+                                              // 2: more colours than the bitmaps hold
+  int32_t round_max[3];            // largest colour given in the round before, modulo 3
+  int32_t pad;
+  unsigned long long cut_list[2][kCgCut];     // {entries, column} by round parity
+  uint32_t cut_beg[2][kCgCut];                // their first entries
+  int32_t done[kCgCut];                       // chunks finished (zero between rounds)
+};
+static_assert(sizeof(uint32_t) * kCgCut * kCgWords + sizeof(ColorCtl) <=
+                  sizeof(uint32_t) * size_t(kFlatMax) * kMexWords,
+              "the control block fits behind the bitmaps");
+
+struct ColorGridArgs {
+  const int64_t *col_ptr;
+  const int4 *ent;                 // per CSC entry: its row's slots [x, z), its own slot y
+  const int32_t *col_at;
+  int32_t *color, *count;
+  int32_t *front_a, *front_b;      // whole columns by round parity
+  uint32_t *bits;                  // [kCgCut][kCgWords], all zero between rounds
+  ColorCtl *ctl;
+};
+
+__global__ __launch_bounds__(kBlock) void k_color_ents(const int32_t *row_idx, int64_t nnz,
+                                                        const int32_t *row_ptr,
+                                                        const int32_t *pos_in_row, int4 *ent) {
+  for (int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x; e < nnz;
+       e += int64_t(gridDim.x) * kBlock) {
+    const int32_t r = row_idx[e], b = row_ptr[r];
+    ent[e] = make_int4(b, b + pos_in_row[e], row_ptr[r + 1], 0);
+  }
+}
+
+// A column whose earlier neighbours all have colours joins a list.
+__device__ __forceinline__ void color_push(const ColorGridArgs &a, int32_t j, int64_t beg,
+                                           int32_t len, int32_t *front, int nx, int par) {
+  if (len > kCgChunk) {
+    const int32_t h = atomicAdd(&a.ctl->cut[nx], 1);
+    if (h < kCgCut) {
+      agent_store(&a.ctl->cut_beg[par][h], uint32_t(beg));
+      agent_store(&a.ctl->cut_list[par][h],
+                  static_cast<unsigned long long>(len) << 32 | uint32_t(j));
+      return;
+    }
+  }
+  agent_store(&front[atomicAdd(&a.ctl->whole[nx], 1)], j);
+}
+
+// The initial frontier (k_init_count's list) and counters for the grid.
+__global__ __launch_bounds__(kBlock) void k_color_start(ColorGridArgs a, const int32_t *front,
+                                                         const int32_t *n, const int32_t *old) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->max_color = old[3];  // 0 where a column is empty
+  for (int32_t i = int32_t(blockIdx.x) * kBlock + threadIdx.x; i < *n;
+       i += int32_t(gridDim.x) * kBlock) {
+    const int32_t j = front[i];
+    const int64_t beg = a.col_ptr[j];
+    color_push(a, j, beg, int32_t(a.col_ptr[j + 1] - beg), a.front_b, 0, 0);
+  }
+}
+
+// Entries [e0, e1) of one column by a wave: colours of the earlier columns of
+// each row into `bits` (LDS, this wave's), later columns into the hash.
+__device__ __forceinline__ void color_walk(const ColorGridArgs &a, int64_t e0, int64_t e1,
+                                           int lane, int32_t words, uint32_t *bits, int32_t *hkey,
+                                           int32_t *hcnt, int32_t *front, int nx, int par) {
+  const int sub = lane / kCgSG, l = lane & (kCgSG - 1);
+  auto later = [&](int32_t j2) {
+    uint32_t h = (uint32_t(j2) * 2654435761u) & (kHash - 1);
+    for (int p = 0; p < kProbe; ++p, h = (h + 1) & (kHash - 1)) {
+      const int32_t prev = atomicCAS(&hkey[h], -1, j2);
+      if (prev == -1 || prev == j2) {
+        atomicAdd(&hcnt[h], 1);
+        return;
+      }
+    }
+    if (atomicSub(&a.count[j2], 1) == 1) {
+      const int64_t beg = a.col_ptr[j2];
+      color_push(a, j2, beg, int32_t(a.col_ptr[j2 + 1] - beg), front, nx, par);
+    }
+  };
+  for (int64_t e = e0; e < e1; e += kCgPer * kCgDeep) {
+    int4 x[kCgDeep];
+#pragma unroll
+    for (int g = 0; g < kCgDeep; ++g) {
+      const int64_t at = e + g * kCgPer + sub;
+      x[g] = a.ent[at < e1 ? at : e0];
+      if (at >= e1) x[g].z = x[g].x;  // nothing
+    }
+    int32_t c[kCgDeep][2], v[kCgDeep][2];
+#pragma unroll
+    for (int g = 0; g < kCgDeep; ++g)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int32_t q = x[g].x + u * kCgSG + l;
+        c[g][u] = q < x[g].z && q != x[g].y ? a.col_at[q] : -1;
+      }
+#pragma unroll
+    for (int g = 0; g < kCgDeep; ++g)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int32_t q = x[g].x + u * kCgSG + l;
+        v[g][u] = c[g][u] >= 0 && q < x[g].y ? agent_load(&a.color[c[g][u]]) : -1;
+      }
+#pragma unroll
+    for (int g = 0; g < kCgDeep; ++g)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int32_t q = x[g].x + u * kCgSG + l;
+        if (v[g][u] >= 0 && v[g][u] < words * 32)
+          atomicOr(&bits[v[g][u] >> 5], 1u << (v[g][u] & 31));
+        if (c[g][u] >= 0 && q > x[g].y) later(c[g][u]);
+      }
+#pragma unroll
+    for (int g = 0; g < kCgDeep; ++g)  // rows of more than 32 entries
+      for (int32_t q = x[g].x + 2 * kCgSG + l; q < x[g].z; q += kCgSG) {
+        if (q == x[g].y) continue;
+        const int32_t j2 = a.col_at[q];
+        if (q > x[g].y) {
+          later(j2);
+        } else {
+          const int32_t w = agent_load(&a.color[j2]);
+          if (w >= 0 && w < words * 32) atomicOr(&bits[w >> 5], 1u << (w & 31));
+        }
+      }
+  }
+}
+
+// Lowest colour not in a bitmap of `words` words (word u from get(u)); the
+// same in every lane.
+template <typename Get>
+__device__ __forceinline__ int32_t color_mex(int32_t words, int lane, Get get) {
+  int32_t mine = words * 32;
+  for (int32_t u = lane; u < words; u += kWave) {
+    const uint32_t free_bits = ~get(u);
+    if (free_bits) {
+      mine = u * 32 + __ffs(int(free_bits)) - 1;
+      break;
+    }
+  }
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) mine = min(mine, __shfl_xor(mine, off));
+  return mine;
+}
+
+__global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
+  __shared__ int sm[2];
+  __shared__ int32_t head[3];
+  __shared__ uint32_t bitmap[kCgWaves][kCgWords];
+  __shared__ int32_t hkey[kHash], hcnt[kHash];
+  int members;
+  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(&a.ctl->g, sm, members));
+  members = __builtin_amdgcn_readfirstlane(members);
+  if (me < 0) return;
+  const int lane = int(threadIdx.x) & (kWave - 1);
+  const int slot = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+  const int wave = slot * members + me, nw = members * kCgWaves;
+  uint32_t *const bits = bitmap[slot];
+  const int32_t r0 = a.ctl->round;
+  // the largest colour so far: every workgroup folds the last round's in, so
+  // all of them size the bitmaps alike while others give colours already
+  int32_t maxc = a.ctl->max_color;
+  int32_t colored = 0, status = 0, r = r0;
+  int bar = 0;
+  for (;; ++r) {
+    const int cur = r % 3, nx = (r + 1) % 3, par = r & 1;
+    int32_t *const front = par ? a.front_a : a.front_b;   // whole columns of this round
+    int32_t *const next = par ? a.front_b : a.front_a;
+    if (threadIdx.x < 3)
+      head[threadIdx.x] = agent_load(threadIdx.x == 0   ? &a.ctl->whole[cur]
+                                     : threadIdx.x == 1 ? &a.ctl->cut[cur]
+                                                        : &a.ctl->round_max[cur]);
+    __syncthreads();
+    const int32_t F = head[0], H = head[1] < kCgCut ? head[1] : kCgCut;
+    maxc = head[2] > maxc ? head[2] : maxc;
+    const int32_t words = (maxc + 2 + 31) / 32;
+    if (F + H == 0) {
+      status = 1;
+      break;
+    }
+    if (words > kCgWords) {
+      status = 2;
+      break;
+    }
+    if (r - r0 >= kCgRounds) break;
+    if (me == 0 && threadIdx.x == 0) {  // counters of the round after next (last read a round ago)
+      agent_store(&a.ctl->whole[(r + 2) % 3], 0);
+      agent_store(&a.ctl->cut[(r + 2) % 3], 0);
+      agent_store(&a.ctl->round_max[(r + 2) % 3], 0);
+    }
+    colored += F + H;
+    if (me < F || H > 0) {  // uniform over the workgroup
+      for (int u = threadIdx.x; u < kHash; u += kCgThreads) {
+        hkey[u] = -1;
+        hcnt[u] = 0;
+      }
+      __syncthreads();
+      for (int32_t i = wave; i < F; i += nw) {
+        const int32_t j = __builtin_amdgcn_readfirstlane(agent_load(&front[i]));
+        for (int32_t u = lane; u < words; u += kWave) bits[u] = 0u;
+        color_walk(a, a.col_ptr[j], a.col_ptr[j + 1], lane, words, bits, hkey, hcnt, next, nx,
+                   par ^ 1);
+        __builtin_amdgcn_wave_barrier();
+        const int32_t c = color_mex(words, lane, [&](int32_t u) { return bits[u]; });
+        if (lane == 0) {
+          agent_store(&a.color[j], c);
+          if (c > maxc) atomicMax(&a.ctl->round_max[nx], c);
+        }
+      }
+      int32_t seen = 0;  // chunks handed out so far, modulo the waves
+      for (int32_t h0 = 0; h0 < H; h0 += kWave) {
+        const unsigned long long v =
+            h0 + lane < H ? agent_load(&a.ctl->cut_list[par][h0 + lane]) : 0ull;
+        const uint32_t vb = h0 + lane < H ? agent_load(&a.ctl->cut_beg[par][h0 + lane]) : 0u;
+        const int nh = H - h0 < kWave ? H - h0 : kWave;
+        for (int g = 0; g < nh; ++g) {
+          const int32_t len = __builtin_amdgcn_readlane(int(v >> 32), g);
+          const int32_t nc = (len + kCgChunk - 1) / kCgChunk;
+          int32_t c = (wave - seen) % nw;
+          for (c += c < 0 ? nw : 0; c < nc; c += nw) {
+            for (int32_t u = lane; u < words; u += kWave) bits[u] = 0u;
+            const int64_t cb = int64_t(uint32_t(__builtin_amdgcn_readlane(int(vb), g)));
+            const int32_t e1 = (c + 1) * kCgChunk < len ? (c + 1) * kCgChunk : len;
+            color_walk(a, cb + int64_t(c) * kCgChunk, cb + e1, lane, words, bits, hkey, hcnt, next,
+                       nx, par ^ 1);
+            __builtin_amdgcn_wave_barrier();
+            uint32_t *const gb = a.bits + int64_t(h0 + g) * kCgWords;
+            for (int32_t u = lane; u < words; u += kWave)
+              if (bits[u]) atomicOr(&gb[u], bits[u]);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            int32_t t = 0;
+            if (lane == 0) t = atomicAdd(&a.ctl->done[h0 + g], 1);
+            if (__builtin_amdgcn_readfirstlane(t) != nc - 1) continue;
+            // the last chunk of its column
+            const int32_t col = __builtin_amdgcn_readlane(int(uint32_t(v)), g);
+            const int32_t m = color_mex(words, lane, [&](int32_t u) { return agent_load(&gb[u]); });
+            if (lane == 0) {
+              agent_store(&a.color[col], m);
+              agent_store(&a.ctl->done[h0 + g], 0);
+              if (m > maxc) atomicMax(&a.ctl->round_max[nx], m);
+            }
+            for (int32_t u = lane; u < words; u += kWave) agent_store(&gb[u], 0u);
+          }
+          seen = (seen + nc) % nw;
+        }
+      }
+      __syncthreads();
+      for (int u = threadIdx.x; u < kHash; u += kCgThreads) {
+        const int32_t key = hkey[u];
+        if (key >= 0) {
+          const int32_t c = hcnt[u];
+          const int64_t beg = a.col_ptr[key], end = a.col_ptr[key + 1];  // beside the atomic
+          if (atomicSub(&a.count[key], c) == c)
+            color_push(a, key, beg, int32_t(end - beg), next, nx, par ^ 1);
+        }
+      }
+    }
+    if (!grid_barrier(&a.ctl->g, &a.ctl->bad, me, members, ++bar, sm)) return;
+  }
+  if (me == 0 && threadIdx.x == 0) {
+    a.ctl->colored += colored;
+    a.ctl->max_color = maxc;
+    a.ctl->round = r;
+    a.ctl->status = status;
+  }
+}
+
+// After status 2: the frontier as one list in front, and the counters of the
+// separate launches.
+__global__ __launch_bounds__(kBlock) void k_color_merge(ColorGridArgs a, int32_t *front,
+                                                         int32_t round, int32_t *ctl) {
+  const int32_t F = a.ctl->whole[round % 3];
+  const int32_t H = min(a.ctl->cut[round % 3], kCgCut);
+  for (int32_t i = threadIdx.x; i < H; i += kBlock)
+    front[F + i] = int32_t(a.ctl->cut_list[round & 1][i]);
+  if (threadIdx.x == 0) {
+    ctl[0] = F + H;
+    ctl[1] = ctl[3] = a.ctl->max_color;
+    ctl[4] = 0;
+    ctl[5] += a.ctl->colored;
+  }
+}
+
+__global__ void k_color_clear_sync(ColorCtl *c) {
+  for (int i = threadIdx.x; i < int(sizeof(GridCtl) / 4); i += int(blockDim.x))
+    reinterpret_cast<int32_t *>(&c->g)[i] = 0;
+}
 
 static unsigned g1(int64_t m, unsigned cap = 4096) {
   int64_t b = (m + kBlock - 1) / kBlock;
@@ -558,7 +893,7 @@ int color_run(const gencd_csc *X, int32_t *color, int32_t *num_colors, void *ws_
   st = fill_i32(w.fcnt, n + 1, 0, s);
   if (st) return st;
   hipLaunchKernelGGL(k_csr_list, dim3(g1(k * kWave, 8192)), dim3(kBlock), 0, s, X->col_ptr,
-                     X->row_idx, k, w.order, w.roff, w.keys_a, w.vals_a, w.erank, w.fcnt);
+                     X->row_idx, k, w.order, w.roff, w.keys_a, w.vals_a, w.ecol, w.fcnt);
   st = scan_exclusive(w.fcnt, w.row_ptr, n, w.scan_part, s);
   if (st) return st;
   if (nnz > 0) {
@@ -566,7 +901,7 @@ int color_run(const gencd_csc *X, int32_t *color, int32_t *num_colors, void *ws_
                           w.rhist, w.roffs, w.scan_part, s, &ob);
     if (st) return st;
     hipLaunchKernelGGL(k_csr_fill, dim3(g1(nnz)), dim3(kBlock), 0, s, ob ? w.keys_b : w.keys_a,
-                       ob ? w.vals_b : w.vals_a, nnz, w.row_ptr, w.erank, w.rank_at, w.pos_in_row);
+                       ob ? w.vals_b : w.vals_a, nnz, w.row_ptr, w.ecol, w.col_at, w.pos_in_row);
   }
   st = fill_i32(w.ctl, 8, 0, s);
   if (st) return st;
@@ -580,6 +915,55 @@ int color_run(const gencd_csc *X, int32_t *color, int32_t *num_colors, void *ws_
   hipLaunchKernelGGL(k_init_count, dim3(g1(k * kWave, 8192)), dim3(kBlock), 0, s, X->col_ptr, k,
                      w.pos_in_row, w.count, color, w.front_a, w.ctl);
   GENCD_HIP(hipGetLastError());
+  // Rounds on the resident grid.  Its frontier, counters and bitmaps live in
+  // the (zeroed) bitmap array of the separate launches, which take over if the
+  // colours outgrow its bitmaps.
+  int32_t *cur = w.front_a, *nxt = w.front_b;
+  int64_t round = 0;
+  int32_t ctl_host[8];
+  if (nnz > 0) {
+    ColorGridArgs ga{};
+    ga.col_ptr = X->col_ptr;
+    ga.ent = reinterpret_cast<const int4 *>(w.keys_a);  // the four sort buffers, free by now
+    ga.col_at = w.col_at;
+    ga.color = color;
+    ga.count = w.count;
+    ga.front_a = w.front_a;
+    ga.front_b = w.front_b;
+    ga.bits = w.gbits;
+    ga.ctl = reinterpret_cast<ColorCtl *>(w.gbits + size_t(kCgCut) * kCgWords);
+    hipLaunchKernelGGL(k_color_ents, dim3(g1(nnz)), dim3(kBlock), 0, s, X->row_idx, nnz, w.row_ptr,
+                       w.pos_in_row, reinterpret_cast<int4 *>(w.keys_a));
+    hipLaunchKernelGGL(k_color_start, dim3(g1(k)), dim3(kBlock), 0, s, ga, w.front_a, w.ctl, w.ctl);
+    GENCD_HIP(hipGetLastError());
+    struct {
+      unsigned long long bad;
+      int32_t whole[3], cut[3], max_color, colored, round, status;
+    } h{};
+    static_assert(sizeof(h) == 48 && offsetof(ColorCtl, status) - offsetof(ColorCtl, bad) == 44,
+                  "read-back layout");
+    for (;;) {
+      hipLaunchKernelGGL(k_color_grid, dim3(kCgGrid), dim3(kCgThreads), 0, s, ga);
+      hipLaunchKernelGGL(k_color_clear_sync, dim3(1), dim3(kBlock), 0, s, ga.ctl);
+      GENCD_HIP(hipGetLastError());
+      GENCD_HIP(hipMemcpyAsync(&h, &ga.ctl->bad, sizeof(h), hipMemcpyDeviceToHost, s));
+      GENCD_HIP(hipMemcpyAsync(ctl_host, w.ctl, sizeof(ctl_host), hipMemcpyDeviceToHost, s));
+      GENCD_HIP(hipStreamSynchronize(s));
+      if (h.bad || h.colored > k || h.round > k + 1) return GENCD_ERR_HIP;
+      if (h.status) break;
+    }
+    if (h.status == 1) {
+      if (ctl_host[5] + int64_t(h.colored) != k) return GENCD_ERR_HIP;
+      *num_colors = h.max_color + 1;
+      return GENCD_OK;
+    }
+    cur = (h.round & 1) ? w.front_a : w.front_b;
+    nxt = (h.round & 1) ? w.front_b : w.front_a;
+    hipLaunchKernelGGL(k_color_merge, dim3(1), dim3(kBlock), 0, s, ga, cur, h.round, w.ctl);
+    GENCD_HIP(hipGetLastError());
+    st = fill_i32(reinterpret_cast<int32_t *>(w.gbits), int64_t(kFlatMax) * kMexWords, 0, s);
+    if (st) return st;
+  }
   // Rounds run without the host: every kernel reads the frontier size from
   // the device (counters by round parity); the host looks at the counters
   // once per kRoundsPerSync rounds.  Rounds past the last frontier find an
@@ -589,9 +973,6 @@ int color_run(const gencd_csc *X, int32_t *color, int32_t *num_colors, void *ws_
   // work; on the Lasso workload 2-8x larger grids were slower, as most
   // rounds are small and every workgroup is dispatched)
   constexpr int32_t kMexGrid = 512, kFlatGrid = 256, kDecGrid = 1024;
-  int32_t *cur = w.front_a, *nxt = w.front_b;
-  int32_t ctl_host[8];
-  int64_t round = 0;
   for (;;) {
     for (int r = 0; r < kRoundsPerSync; ++r, ++round) {
       int32_t *fc = w.ctl + ((round & 1) ? 4 : 0), *fn = w.ctl + ((round & 1) ? 0 : 4);
@@ -605,8 +986,8 @@ int color_run(const gencd_csc *X, int32_t *color, int32_t *num_colors, void *ws_
       // readiness counts in one launch; then the small form's pick, which
       // also ends the round
       hipLaunchKernelGGL(k_round_work, dim3(kMexGrid + kFlatGrid + kDecGrid), dim3(kBlock), 0, s,
-                         fc, X->col_ptr, X->row_idx, cur, w.foff, w.row_ptr, w.rank_at,
-                         w.pos_in_row, w.order, color, w.ctl, w.gbits, w.count, nxt, fn,
+                         fc, X->col_ptr, X->row_idx, cur, w.foff, w.row_ptr, w.col_at,
+                         w.pos_in_row, color, w.ctl, w.gbits, w.count, nxt, fn,
                          kMexGrid, kFlatGrid);
       hipLaunchKernelGGL(k_mex_pick, dim3(kFlatMax), dim3(kBlock), 0, s, fc, cur, color, w.ctl,
                          w.gbits);
