@@ -482,7 +482,8 @@ typedef struct {
   int32_t running, waiting, finished_unpolled;
   size_t arena_used, arena_bytes;
   int64_t rounds;        /* rounds so far (a Propose and an Update launch, or one
-                            launch when every request of the round is fused) */
+                            launch when every request of the round is fused, or a
+                            share of a launch that runs several rounds) */
   int64_t slot_rounds;   /* sum over rounds of the requests each advanced */
   int64_t shared_rounds; /* rounds that advanced two or more requests */
 } gencd_server_status;

@@ -721,7 +721,7 @@ __global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
   __shared__ uint32_t bitmap[kCgWaves][kCgWords];
   __shared__ int32_t hkey[kHash], hcnt[kHash];
   int members;
-  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(&a.ctl->g, sm, members));
+  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(&a.ctl->g, int(gridDim.x), sm, members));
   members = __builtin_amdgcn_readfirstlane(members);
   if (me < 0) return;
   const int lane = int(threadIdx.x) & (kWave - 1);

@@ -35,17 +35,6 @@
 
 namespace gencd {
 
-typedef int int4v __attribute__((ext_vector_type(4)));
-
-// The packed rows as a buffer: 16-byte loads with the agent-scope policy.
-struct Rows {
-  __amdgpu_buffer_rsrc_t r;
-};
-__device__ __forceinline__ float4 row_load(const Rows &z, int32_t i) {
-  const int4v v = __builtin_amdgcn_raw_buffer_load_b128(z.r, i * 16, 0, 16);
-  return make_float4(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z), 0.0f);
-}
-
 // Compensated update of a row that this lane owns in the window (columns of a
 // colour class have disjoint rows), from its values at the window's start.
 __device__ __forceinline__ void row_store(float4 *zs, int32_t i, float hi, float lo, float d,
@@ -193,7 +182,7 @@ __global__ __launch_bounds__(kGridThreads) void k_epoch_grid(IterArgs a, GridCtl
                                                         unsigned long long *bad, int32_t T) {
   __shared__ int sm[2];
   int members;
-  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(ctl, sm, members));
+  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(ctl, int(gridDim.x), sm, members));
   members = __builtin_amdgcn_readfirstlane(members);
   if (me < 0) return;
   // waves numbered slot-major: consecutive units go to different workgroups
@@ -425,7 +414,7 @@ __global__ __launch_bounds__(kGridThreads) void k_greedy_grid(IterArgs a, GridCt
   __shared__ int sm[2];
   __shared__ int smb[2];
   int members;
-  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(ctl, sm, members));
+  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(ctl, int(gridDim.x), sm, members));
   members = __builtin_amdgcn_readfirstlane(members);
   if (me < 0) return;
   const int lane = int(threadIdx.x) & (kWave - 1);

@@ -20,12 +20,13 @@ constexpr int kGridPolls = 1 << 22;      // about 2 s; a barrier takes about a m
 constexpr int kEnrollPolls = 4096;       // about 2 ms for the whole grid to start
 constexpr int32_t kClosed = 1 << 20;     // above any number of workgroups
 
-// Members of the grid: this workgroup's index (-1: not one of them).
-__device__ __forceinline__ int grid_enroll(GridCtl *c, int *sm, int &members) {
+// Members of the grid of up to `want` workgroups: this workgroup's index (-1:
+// not one of them).
+__device__ __forceinline__ int grid_enroll(GridCtl *c, int want, int *sm, int &members) {
   if (threadIdx.x == 0) {
     int idx = atomicAdd(&c->count, 1), m = 0;
     if (idx == 0) {
-      for (int p = 0; p < kEnrollPolls && agent_load(&c->count) < int(gridDim.x); ++p)
+      for (int p = 0; p < kEnrollPolls && agent_load(&c->count) < want; ++p)
         __builtin_amdgcn_s_sleep(2);
       m = atomicAdd(&c->count, kClosed);
       agent_store(&c->members, m);
@@ -64,6 +65,17 @@ __device__ __forceinline__ bool grid_barrier(GridCtl *c, unsigned long long *bad
   }
   __syncthreads();
   return sm[0] != 0;
+}
+
+typedef int int4v __attribute__((ext_vector_type(4)));
+
+// The packed rows as a buffer: 16-byte loads with the agent-scope policy.
+struct Rows {
+  __amdgpu_buffer_rsrc_t r;
+};
+__device__ __forceinline__ float4 row_load(const Rows &z, int32_t i) {
+  const int4v v = __builtin_amdgcn_raw_buffer_load_b128(z.r, i * 16, 0, 16);
+  return make_float4(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z), 0.0f);
 }
 
 }  // namespace gencd

@@ -7,7 +7,8 @@
 // advance together: every round is ONE Propose launch and ONE Update launch
 // over a device work table of (request slot, window position range) items,
 // so a single dispatch carries one Jacobi iteration (Algorithm 2 / 4, then
-// Algorithm 3) of every admitted request.  A request's state (w, packed
+// Algorithm 3) of every admitted request; up to a size, ONE launch carries
+// several such rounds on teams of resident workgroups.  A request's state (w, packed
 // z_hi/z_lo/y, curvature, epoch order, FP64 check arrays) stays resident in
 // the arena from admission to retirement.
 //
@@ -36,8 +37,7 @@
 #include <thread>
 #include <vector>
 
-#include "gencd_common.hpp"
-#include "gencd_kernels.hpp"
+#include "gencd_gridsync.hpp"
 #include "gencd_solver.hpp"
 
 namespace gencd {
@@ -144,20 +144,23 @@ class Admission {
 
 // One admitted request as the round kernels see it.
 struct MpSlot {
-  const int64_t *col_ptr;
   const int32_t *row_idx;
   const float *val;
-  const float *c;          // curvature beta ||X_j||^2 / n
   float *w;                // the caller's weights (the live iterate)
   float4 *zs;              // {z_hi, z_lo, y, 0} per row
-  const int32_t *col_of_pos;  // current epoch order of the live columns
+  const int4 *order;       // current epoch order of the live columns: {first entry, column,
+                           // entries, curvature}
   float *delta;            // increments of the current window
   int64_t r0;              // round at which the slot's epoch 0 started
   int64_t T;               // windows per epoch
   float lam, n_f;
   int32_t loss, G;         // G: lanes per column (4..64, from the mean column length)
   int32_t S, k_live;       // |J| and the live column count
-  int32_t fused, pad_;     // fused: Propose scatters each step at once (GENCD_FUSED)
+  int32_t fused;           // Propose scatters each step at once (GENCD_FUSED)
+  int32_t team, Gt;        // resident rounds: workgroups, lanes per column
+  int64_t n;
+  GridCtl *ctl;            // [2] by launch parity (resident rounds)
+  unsigned long long *bad; // bit 16: a barrier ran out
 };
 
 // Work item (one wave): slot, window-relative positions [lo, hi).  A wave
@@ -190,13 +193,13 @@ __global__ __launch_bounds__(kBlock) void k_mp_round(const MpSlot *slots, const 
   const int G = sl.G, per = kWave / G, gl = lane & (G - 1);
   const int32_t hi = min(P0 + it.z, P1);
   for (int32_t p = P0 + it.y + lane / G; p < hi; p += per) {
-    const int32_t j = sl.col_of_pos[p];
-    const int64_t b = sl.col_ptr[j];
-    const int32_t len = int32_t(sl.col_ptr[j + 1] - b);
+    const int4 ord = sl.order[p];
+    const int32_t j = ord.y, len = ord.z;
+    const int64_t b = int64_t(uint32_t(ord.x));
     int32_t ri[kUnroll];
     float vv[kUnroll];
     if constexpr (!UPD) {
-      const float wj = sl.w[j], cj = sl.c[j];
+      const float wj = sl.w[j], cj = __int_as_float(ord.w);
       float s = 0.0f;
       for (int32_t base = 0; base < len; base += G * kUnroll) {
 #pragma unroll
@@ -256,14 +259,223 @@ __global__ __launch_bounds__(kBlock) void k_mp_round(const MpSlot *slots, const 
   }
 }
 
+// Resident rounds: one launch advances every slot by R windows.  A round of two
+// launches is 15 us on a few slots with windows of 10k entries, nearly all of it
+// the launches and four dependent loads in each; here each slot has a team of
+// workgroups (gencd_gridsync.hpp) of its own that meets at two barriers a
+// window, and a wave loads the next window's columns while it works on this
+// one.  Teams do not wait for each other.  Work unit of a wave: 64 / G columns,
+// kUnroll entries per lane in registers, the rest of a longer column from
+// memory; units past the team's waves go through delta.
+constexpr int kTeamThreads = 1024;
+constexpr int kTeamWaves = kTeamThreads / kWave;
+
+struct TeamCol {
+  int4 d;  // {first entry, column, entries, curvature}; entries 0: nothing to do
+  float w;
+  int32_t ri[kUnroll];
+  float vv[kUnroll];
+};
+
+template <int G>
+__device__ void mp_team(const MpSlot &sl, GridCtl *ctl, int me, int members, int32_t t, int32_t R,
+                        int *sm) {
+  const int lane = int(threadIdx.x) & (kWave - 1), gl = lane & (G - 1);
+  const int slot = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+  const int wave = slot * members + me, nw = members * kTeamWaves;
+  const int32_t S = sl.S, kl = sl.k_live, t1 = t + R, loss = sl.loss;
+  constexpr int32_t per = kWave / G;
+  const float n_f = sl.n_f, lam = sl.lam;
+  const Rows z{__builtin_amdgcn_make_buffer_rsrc(sl.zs, 0, int(sl.n * 16), 0x00027000)};
+  float4 *const zs = sl.zs;
+  float *const w = sl.w, *const delta = sl.delta;
+  const int4 *const order = sl.order;
+  const int32_t *const row_idx = sl.row_idx;
+  const float *const val = sl.val;
+  // position of this lane's group in unit u of window v, or -1
+  auto pos = [&](int32_t v, int32_t u) -> int32_t {
+    const int32_t q = u * per + lane / G;
+    const int32_t p = v * S + q;
+    return v < t1 && q < S && p < kl ? p : -1;
+  };
+  auto desc = [&](int32_t v, int32_t u) {
+    const int32_t p = pos(v, u);
+    return p >= 0 ? order[p] : make_int4(0, 0, 0, 0);
+  };
+  auto batch = [&](const int4 &d, int32_t base, int32_t(&ri)[kUnroll], float(&vv)[kUnroll]) {
+    const int64_t b = int64_t(uint32_t(d.x));
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int32_t e = base + u * G + gl;
+      const int64_t at = b + (e < d.z ? e : 0);
+      ri[u] = row_idx[at];
+      vv[u] = val[at];
+    }
+  };
+  auto fill = [&](TeamCol &x) {
+    if (!__any(x.d.z > 0)) return;
+    x.w = w[x.d.y];
+    batch(x.d, 0, x.ri, x.vv);
+  };
+  auto dot = [&](const int4 &d, int32_t base, const int32_t(&ri)[kUnroll],
+                 const float(&vv)[kUnroll]) {
+    float4 r[kUnroll];
+    float s = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) r[u] = row_load(z, ri[u]);
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+      if (base + u * G + gl < d.z) s += vv[u] * dloss_f32(loss, r[u].z, r[u].x + r[u].y);
+    return s;
+  };
+  auto add = [&](const int4 &d, int32_t base, const int32_t(&ri)[kUnroll],
+                 const float(&vv)[kUnroll], float de) {
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+      if (base + u * G + gl < d.z) atomicAdd(&zs[ri[u]].y, de * vv[u]);
+  };
+  auto sum = [&](float s) {
+    if constexpr (G <= 16)
+      return row_group_sum<G>(s);
+    else
+      return group_sum<G>(s);
+  };
+  TeamCol cur, nxt;
+  cur.d = desc(t, wave);
+  nxt.d = desc(t + 1, wave);
+  fill(cur);
+  for (int round = 0; t < t1; ++t) {
+    const int32_t P0 = t * S;
+    const int32_t nu = (min(S, kl - P0) + per - 1) / per;
+    // Propose: rows of this window first, then the next window's loads
+    float4 r[kUnroll];
+    if (wave < nu) {
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) r[u] = row_load(z, cur.ri[u]);
+    }
+    fill(nxt);
+    const int4 dd = desc(t + 2, wave);
+    float d = 0.0f, ph;
+    if (wave < nu) {
+      float s = 0.0f;
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u)
+        if (u * G + gl < cur.d.z) s += cur.vv[u] * dloss_f32(loss, r[u].z, r[u].x + r[u].y);
+      for (int32_t base = G * kUnroll; base < cur.d.z; base += G * kUnroll) {
+        int32_t ri[kUnroll];
+        float vv[kUnroll];
+        batch(cur.d, base, ri, vv);
+        s += dot(cur.d, base, ri, vv);
+      }
+      propose_f32(sum(s) / n_f, __int_as_float(cur.d.w), cur.w, lam, d, ph);
+      if (cur.d.z == 0) d = 0.0f;
+    }
+    for (int32_t u = wave + nw; u < nu; u += nw) {
+      const int32_t p = pos(t, u);
+      const int4 x = desc(t, u);
+      float s = 0.0f, de;
+      for (int32_t base = 0; base < x.z; base += G * kUnroll) {
+        int32_t ri[kUnroll];
+        float vv[kUnroll];
+        batch(x, base, ri, vv);
+        s += dot(x, base, ri, vv);
+      }
+      s = sum(s);
+      if (x.z == 0) continue;
+      const float wj = w[x.y];
+      propose_f32(s / n_f, __int_as_float(x.w), wj, lam, de, ph);
+      if (gl == 0) {
+        delta[p - P0] = de;
+        if (de != 0.0f) w[x.y] = wj + de;
+      }
+    }
+    if (!grid_barrier(ctl, sl.bad, me, members, ++round, sm)) return;
+    // Update
+    if (d != 0.0f) {
+      if (gl == 0) w[cur.d.y] = cur.w + d;
+      add(cur.d, 0, cur.ri, cur.vv, d);
+      for (int32_t base = G * kUnroll; base < cur.d.z; base += G * kUnroll) {
+        int32_t ri[kUnroll];
+        float vv[kUnroll];
+        batch(cur.d, base, ri, vv);
+        add(cur.d, base, ri, vv, d);
+      }
+    }
+    for (int32_t u = wave + nw; u < nu; u += nw) {
+      const int32_t p = pos(t, u);
+      const int4 x = desc(t, u);
+      if (x.z == 0) continue;
+      const float de = delta[p - P0];
+      if (de == 0.0f) continue;
+      for (int32_t base = 0; base < x.z; base += G * kUnroll) {
+        int32_t ri[kUnroll];
+        float vv[kUnroll];
+        batch(x, base, ri, vv);
+        add(x, base, ri, vv, de);
+      }
+    }
+    if (t + 1 < t1 && !grid_barrier(ctl, sl.bad, me, members, ++round, sm)) return;
+    cur = nxt;
+    nxt.d = dd;
+  }
+}
+
+__global__ __launch_bounds__(kTeamThreads) void k_mp_team(const MpSlot *slots, const int4 *items,
+                                                          int64_t round, int32_t R, int parity) {
+  __shared__ int sm[2];
+  const MpSlot &sl = slots[items[blockIdx.x].x];
+  GridCtl *const ctl = sl.ctl + parity;
+  int members;
+  const int me = __builtin_amdgcn_readfirstlane(grid_enroll(ctl, sl.team, sm, members));
+  members = __builtin_amdgcn_readfirstlane(members);
+  if (me < 0) return;
+  if (me == 0)  // the other parity's block, unused in this launch, for the next one
+    for (int i = int(threadIdx.x); i < int(sizeof(GridCtl) / 4); i += kTeamThreads)
+      agent_store(reinterpret_cast<int32_t *>(sl.ctl + (parity ^ 1)) + i, 0);
+  const int32_t t = __builtin_amdgcn_readfirstlane(int32_t((round - sl.r0) % sl.T));
+  switch (sl.Gt) {
+    case 4: return mp_team<4>(sl, ctl, me, members, t, R, sm);
+    case 8: return mp_team<8>(sl, ctl, me, members, t, R, sm);
+    case 16: return mp_team<16>(sl, ctl, me, members, t, R, sm);
+    case 32: return mp_team<32>(sl, ctl, me, members, t, R, sm);
+    default: return mp_team<64>(sl, ctl, me, members, t, R, sm);
+  }
+}
+
+// Which tables take resident rounds, and a slot's team: workgroups for
+// kTeamShare units each (a CU gathers and scatters the rows of a few waves, not
+// of 16, in the barriers' time), up to kTeamMax; more units each where many
+// slots share the chip at one workgroup per CU.  Per round, two launches ->
+// teams: one request with windows of 12k entries 16.0 -> 5.9 us, 96k 14.6 to
+// 18.5 -> 8.2 to 11.1, 160k 15.2 -> 10.3, 320k 17.9 -> 16.7, 640k 23.1 -> 26.8;
+// four of 48k 19.1 -> 9.2, four of 320k 25.3 -> 19.0; 30 of 6k 33.4 -> 12.3.
+// With one window per epoch, a launch each: four of 64k 39.5 -> 33.4.
+constexpr int32_t kTeamMax = 64, kTeamTotal = 240;
+constexpr double kTeamNnz = 262144.0;
+constexpr int64_t kTeamShare = 2;
+constexpr int64_t kTeamRounds = 32;  // windows per launch: about 0.2 ms, so that results and new
+                                     // requests do not wait long
+
+static int32_t team_group(int64_t nnz, int64_t k_live) {
+  const double mean = k_live > 0 ? double(nnz) / double(k_live) : 1.0;
+  int32_t g = 4;  // most columns end inside a lane's kUnroll entries
+  while (g < kWave && double(g) * kUnroll < mean + 3.0 * std::sqrt(mean)) g *= 2;
+  return g;
+}
+
 // Epoch order of one slot: position p holds live column live[pi_e(p)], the
 // same keyed Feistel permutation (section 2.1's random subsets) as the
 // single-problem solve.
 __global__ __launch_bounds__(kBlock) void k_mp_order(const int32_t *live, int64_t k_live, PermKey pk,
-                                                     int32_t *col_of_pos) {
+                                                     const int64_t *col_ptr, const float *c,
+                                                     int4 *order) {
   for (int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x; p < k_live;
-       p += int64_t(gridDim.x) * kBlock)
-    col_of_pos[p] = live[perm_apply(pk, uint64_t(p))];
+       p += int64_t(gridDim.x) * kBlock) {
+    const int32_t j = live[perm_apply(pk, uint64_t(p))];
+    const int64_t b = col_ptr[j];
+    order[p] = make_int4(int32_t(uint32_t(b)), j, int32_t(col_ptr[j + 1] - b),
+                         __float_as_int(c[j]));
+  }
 }
 
 static unsigned grid_of(int64_t m, unsigned cap = 4096) {
@@ -273,11 +485,12 @@ static unsigned grid_of(int64_t m, unsigned cap = 4096) {
   return unsigned(b);
 }
 
-static int enqueue_order(const Setup &su, uint64_t seed, int64_t epoch, hipStream_t s) {
+static int enqueue_order(const gencd_csc &X, const Setup &su, uint64_t seed, int64_t epoch,
+                         hipStream_t s) {
   if (su.k_live <= 0) return GENCD_OK;
   const PermKey pk = make_perm_key(su.k_live, seed, epoch);
   hipLaunchKernelGGL(k_mp_order, dim3(grid_of(su.k_live)), dim3(kBlock), 0, s, su.ws.live,
-                     su.k_live, pk, su.ws.col_of_pos);
+                     su.k_live, pk, X.col_ptr, su.ws.c, su.ws.desc_s);
   return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
 }
 
@@ -457,7 +670,10 @@ void gencd_server::admission_loop() {
     if (!st && !done_now) {
       st = copy_f32(sl.w_best, sl.req.w, X->k, s);
       if (!st) st = copy_f32(sl.su.ws.w_ckpt, sl.req.w, X->k, s);
-      if (!st) st = enqueue_order(sl.su, p.seed, 0, s);
+      if (!st) st = enqueue_order(*X, sl.su, p.seed, 0, s);
+      if (!st)  // the teams' control blocks
+        st = fill_i32(reinterpret_cast<int32_t *>(sl.su.ws.scat),
+                      int64_t(2 * sizeof(GridCtl) / sizeof(int32_t)), 0, s);
     }
     if (!st && done_now && sl.req.z) st = launch_round_f32(sl.su.ws.z64, sl.req.z, X->n, s);
     if (hipStreamSynchronize(s) != hipSuccess && !st) st = GENCD_ERR_HIP;
@@ -485,6 +701,8 @@ void gencd_server::driver_loop() {
   int fail = GENCD_OK;
   bool dirty = false;
   bool all_fused = false;  // every slot of the work table is fused: no Update launch
+  bool teams = false;      // resident rounds
+  int64_t launches = 0, team_launches = 0;
   const int Q = int(ev_round.size());
   int stage_next = 0;
 
@@ -498,6 +716,10 @@ void gencd_server::driver_loop() {
     CheckOut ck{};
     Red red{};
     std::memcpy(&red, sl.h_rep + kChkRep * 16, sizeof(Red));
+    if (red.bad & 16ull) {  // a team's barrier ran out: the state is not valid
+      fail = GENCD_ERR_HIP;
+      return KEEP;
+    }
     fold_check(sl.h_rep, red, sl.req.X.n, sl.req.params.lambda, &ck);
     const gencd_params &p = sl.req.params;
     gencd_stats &so = sl.res.stats;
@@ -512,7 +734,7 @@ void gencd_server::driver_loop() {
         fail = launch_check(&sl.req.X, sl.req.y, p.loss, p.lambda, sl.req.w, sl.su.n_short,
                             sl.su.n_lpieces, sl.su.ws, true, stream);
       if (!fail) fail = copy_f32(sl.su.ws.w_ckpt, sl.req.w, k, stream);
-      if (!fail) fail = enqueue_order(sl.su, p.seed, sl.epoch, stream);
+      if (!fail) fail = enqueue_order(sl.req.X, sl.su, p.seed, sl.epoch, stream);
       sl.S = (sl.S + 1) / 2;
       sl.T = (sl.su.k_live + sl.S - 1) / sl.S;
       sl.in_epoch = 0;
@@ -607,17 +829,16 @@ void gencd_server::driver_loop() {
       int32_t nitems = 0;
       const int32_t budget = std::max<int32_t>(1, max_items / max_slots);
       all_fused = true;
+      teams = true;
       for (int si : active) {
         Slot &sl = slots[size_t(si)];
         const Ws &w = sl.su.ws;
         MpSlot &d = sl.dev;
-        d.col_ptr = sl.req.X.col_ptr;
         d.row_idx = sl.req.X.row_idx;
         d.val = sl.req.X.val;
-        d.c = w.c;
         d.w = sl.req.w;
         d.zs = w.zs;
-        d.col_of_pos = w.col_of_pos;
+        d.order = w.desc_s;
         d.delta = w.delta;
         d.T = sl.T;
         d.lam = float(sl.req.params.lambda);
@@ -627,9 +848,32 @@ void gencd_server::driver_loop() {
         d.S = int32_t(sl.S);
         d.k_live = int32_t(sl.su.k_live);
         d.fused = (sl.req.params.flags & GENCD_FUSED) ? 1 : 0;
-        d.pad_ = 0;
+        d.n = sl.req.X.n;
+        d.ctl = reinterpret_cast<GridCtl *>(w.scat);
+        d.bad = reinterpret_cast<unsigned long long *>(w.red) + 10;
         all_fused = all_fused && d.fused;
+        d.Gt = team_group(sl.req.X.nnz, sl.su.k_live);
+        teams = teams && !d.fused && d.n <= INT32_MAX / 16 &&
+                double(sl.S) * double(sl.req.X.nnz) <= kTeamNnz * double(sl.su.k_live);
+      }
+      for (int64_t share = kTeamShare; teams; share *= 2) {
+        int32_t blocks = 0;
+        for (int si : active) {
+          MpSlot &d = slots[size_t(si)].dev;
+          const int64_t units = (d.S + kWave / d.Gt - 1) / (kWave / d.Gt);
+          d.team = int32_t(std::min<int64_t>((units + share - 1) / share, kTeamMax));
+          blocks += d.team;
+        }
+        if (blocks <= kTeamTotal) break;
+        teams = share < kTeamWaves;
+      }
+      for (int si : active) {
+        MpSlot &d = slots[size_t(si)].dev;
         sg.slots[si] = d;
+        if (teams) {
+          for (int32_t b = 0; b < d.team; ++b) sg.items[nitems++] = make_int4(si, 0, 0, 0);
+          continue;
+        }
         int32_t span = (kWave / d.G) * kMpRoundsPerItem;
         const int32_t need = (d.S + budget - 1) / budget;  // at most `budget` items per slot
         if (span < need) span = need;
@@ -648,27 +892,40 @@ void gencd_server::driver_loop() {
       dirty = false;
     }
     // 4. one round: every active slot advances one window, one launch each
-    //    for Propose and Update; at most Q rounds are in flight
-    if (rounds >= Q) (void)hipEventSynchronize(ev_round[size_t(rounds % Q)]);
-    const unsigned grid = unsigned((cur_items + (kBlock / kWave) - 1) / (kBlock / kWave));
-    hipLaunchKernelGGL(k_mp_round<false>, dim3(grid), dim3(kBlock), 0, stream, d_slots, d_items,
-                       cur_items, rounds);
-    if (!all_fused)  // fused slots scattered their steps in the Propose launch
-      hipLaunchKernelGGL(k_mp_round<true>, dim3(grid), dim3(kBlock), 0, stream, d_slots, d_items,
+    //    for Propose and Update, or R windows in a launch of the teams; at
+    //    most Q launches (pairs) are in flight
+    if (launches >= Q) (void)hipEventSynchronize(ev_round[size_t(launches % Q)]);
+    int64_t R = 1;
+    if (teams) {  // up to the first epoch end
+      R = kTeamRounds;
+      for (int si : active) R = std::min(R, slots[size_t(si)].T - slots[size_t(si)].in_epoch);
+      hipLaunchKernelGGL(k_mp_team, dim3(unsigned(cur_items)), dim3(kTeamThreads), 0, stream,
+                         d_slots, d_items, rounds, int32_t(R), int(team_launches & 1));
+      ++team_launches;
+    } else {
+      const unsigned grid = unsigned((cur_items + (kBlock / kWave) - 1) / (kBlock / kWave));
+      hipLaunchKernelGGL(k_mp_round<false>, dim3(grid), dim3(kBlock), 0, stream, d_slots, d_items,
                          cur_items, rounds);
-    if (hipGetLastError() != hipSuccess || hipEventRecord(ev_round[size_t(rounds % Q)], stream) != hipSuccess) {
+      if (!all_fused)  // fused slots scattered their steps in the Propose launch
+        hipLaunchKernelGGL(k_mp_round<true>, dim3(grid), dim3(kBlock), 0, stream, d_slots, d_items,
+                           cur_items, rounds);
+    }
+    if (hipGetLastError() != hipSuccess ||
+        hipEventRecord(ev_round[size_t(launches % Q)], stream) != hipSuccess) {
       fail = GENCD_ERR_HIP;
       continue;
     }
-    ++rounds;
-    slot_rounds += int64_t(active.size());
-    shared_rounds += active.size() > 1 ? 1 : 0;
+    launches += 1;
+    rounds += R;
+    slot_rounds += R * int64_t(active.size());
+    shared_rounds += active.size() > 1 ? R : 0;
     // 5. epoch ends: fold the previous check first, then the FP64 check of
     //    this epoch (z re-sync) with its read-back, and the next order
     for (size_t a = 0; a < active.size();) {
       const int si = active[a];
       Slot &sl = slots[size_t(si)];
-      if (++sl.in_epoch < sl.T) {
+      sl.in_epoch += R;
+      if (sl.in_epoch < sl.T) {
         ++a;
         continue;
       }
@@ -705,7 +962,7 @@ void gencd_server::driver_loop() {
       } else if (!fail) {
         fail = launch_renorm(sl.req.X.n, sl.su.ws.zs, stream);
       }
-      if (!fail) fail = enqueue_order(sl.su, p.seed, sl.epoch, stream);
+      if (!fail) fail = enqueue_order(sl.req.X, sl.su, p.seed, sl.epoch, stream);
       ++a;
     }
   }
