@@ -134,6 +134,34 @@ __host__ __device__ __forceinline__ uint64_t perm_apply(const PermKey &pk, uint6
   return x;
 }
 
+// The round functions of a key as a table in LDS, f[r << half | x], for
+// half <= kPermTableHalf.  Walking back into the domain takes a wave as many
+// steps as its unluckiest lane; a step is four LDS reads instead of four
+// rounds of 64-bit multiplications.
+constexpr int kPermTableHalf = 11;  // domains of up to 2^22
+__device__ __forceinline__ void perm_table(const PermKey &pk, uint16_t *f, int tid, int nt) {
+  const uint32_t mask = (1u << pk.half) - 1u;
+  for (uint32_t i = uint32_t(tid); i < (4u << pk.half); i += uint32_t(nt))
+    f[i] = uint16_t(uint32_t(splitmix_fin(uint64_t(i & mask) ^ pk.k[i >> pk.half])) & mask);
+}
+
+__device__ __forceinline__ uint32_t perm_apply_table(const PermKey &pk, const uint16_t *f,
+                                                     uint32_t x) {
+  const int h = pk.half;
+  const uint32_t mask = (1u << h) - 1u;
+  do {
+    uint32_t L = x >> h, R = x & mask;
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) {
+      const uint32_t t = R;
+      R = L ^ f[(r << h) + R];
+      L = t;
+    }
+    x = (L << h) | R;
+  } while (x >= uint32_t(pk.m));
+  return x;
+}
+
 // ---------------------------------------------------------------------------
 // Reductions inside an aligned group of G lanes of a wave64.
 // ---------------------------------------------------------------------------

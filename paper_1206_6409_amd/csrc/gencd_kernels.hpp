@@ -120,12 +120,10 @@ int launch_curvature(const gencd_csc *X, int loss, int32_t n_short, int32_t n_lp
 int launch_select_perm(int64_t m, uint64_t seed, int64_t epoch, int32_t *out, hipStream_t s);
 // Writes the epoch order, its piece descriptors and, in w.wbounds[0..T], the
 // first piece of every window (S positions per window; colour windows for
-// COLORING).
-int launch_epoch_order(const Ws &w, int64_t k_live, int rule, uint64_t seed,
-                       const int64_t *epoch, int64_t num_colors, int64_t S, int64_t T,
-                       hipStream_t s);
-// Epoch counter + 1; ctl (may be null): cleared for the next epoch's grid.
-int launch_inc_epoch(int64_t *epoch, hipStream_t s, GridCtl *ctl = nullptr);
+// COLORING).  Then the epoch counter steps, and ctl (may be null) is cleared
+// for the epoch's grid.
+int launch_epoch_order(const Ws &w, int64_t k_live, int rule, uint64_t seed, int64_t *epoch,
+                       GridCtl *ctl, int64_t num_colors, int64_t S, int64_t T, hipStream_t s);
 int launch_list_order(const Ws &w, const int32_t *J, int64_t nJ, hipStream_t s);
 // group: lanes per short column (4, 8, 16 or 32); short_bound / long_bound:
 // expected short columns / long pieces of a window (they size the grid; the
@@ -151,8 +149,8 @@ int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws 
 int launch_block_setup(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws &ws,
                        int64_t k_live, uint64_t seed, int iters, hipStream_t s);
 // Per-epoch order of Block Shotgun (col_of_pos, windows win_off[0..T]).
-int launch_block_order(const Ws &w, int64_t k_live, uint64_t seed, const int64_t *epoch, int64_t T,
-                       hipStream_t s);
+int launch_block_order(const Ws &w, int64_t k_live, uint64_t seed, int64_t *epoch, GridCtl *ctl,
+                       int64_t T, hipStream_t s);
 int launch_check(const gencd_csc *X, const float *y, int loss, double lam, const float *w,
                  int32_t n_short, int32_t n_lpieces, const Ws &ws, bool resync, hipStream_t s);
 int launch_renorm(int64_t n, float4 *zs, hipStream_t s);

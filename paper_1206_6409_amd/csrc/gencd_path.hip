@@ -1086,7 +1086,7 @@ int path_run(const gencd_csc *X, const float *y, const gencd_params *p, const do
     if (u >= 0 && pev.v[size_t(u) + 1]) (void)hipEventRecord(pev.v[size_t(u) + 1], es);
   };
   auto enqueue_epoch = [&](hipStream_t es) -> int {
-    int rc = launch_epoch_order(ws, k_live, GENCD_SHOTGUN, p->seed, epoch_dev, 0, S, T, es);
+    int rc = launch_epoch_order(ws, k_live, GENCD_SHOTGUN, p->seed, epoch_dev, nullptr, 0, S, T, es);
     if (rc) return rc;
     hipLaunchKernelGGL(k_path_desc, dim3(g1(k_live)), dim3(kBlock), 0, es, k_live, ws.col_of_pos,
                        X->col_ptr, ws.desc_s);
@@ -1124,8 +1124,6 @@ int path_run(const gencd_csc *X, const float *y, const gencd_params *p, const do
       tstop(es, u1);
     }
     hipLaunchKernelGGL(k_path_renorm<B>, dim3(g1(n * B)), dim3(kBlock), 0, es, n * B, w.zh, w.zl);
-    rc = launch_inc_epoch(epoch_dev, es);
-    if (rc) return rc;
     return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
   };
   PathGraph graph;

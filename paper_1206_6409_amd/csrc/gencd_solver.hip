@@ -688,18 +688,15 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
            !wants_rs(p, positions, X->nnz, k_live, X->n) && grid_fits(X->nnz, k_live, positions, mode == 2);
   };
   GridCtl *const gctl = reinterpret_cast<GridCtl *>(ws.scat);  // profiling counters otherwise
-  if (!prof) {
-    st = fill_i32(reinterpret_cast<int32_t *>(gctl), int64_t(sizeof(GridCtl) / 4), 0, s);
-    if (st) return st;
-  }
 
-  // Enqueue one epoch: selection order (section 2.1), then every iteration
-  // of Algorithm 1, then the epoch counter increment.  Every argument is
+  // Enqueue one epoch: selection order (section 2.1) and the epoch counter's
+  // increment, then every iteration of Algorithm 1.  Every argument is
   // independent of the epoch number, so the sequence can be captured once.
   auto enqueue_epoch = [&](int64_t T, int64_t e_host, bool record, hipStream_t es) -> int {
     int rc = rule == GENCD_BLOCK_SHOTGUN
-                 ? launch_block_order(ws, k_live, p->seed, epoch_dev, T, es)
-                 : launch_epoch_order(ws, k_live, rule, p->seed, epoch_dev, C, S, T, es);
+                 ? launch_block_order(ws, k_live, p->seed, epoch_dev, prof ? nullptr : gctl, T, es)
+                 : launch_epoch_order(ws, k_live, rule, p->seed, epoch_dev,
+                                      prof ? nullptr : gctl, C, S, T, es);
     if (rc) return rc;
     const int64_t mean_pos = T > 0 ? (k_live + T - 1) / T : 0;
     const bool grid = T > 1 && grid_ok(mean_pos);
@@ -761,7 +758,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       rc = launch_renorm(X->n, ws.zs, es);
       if (rc) return rc;
     }
-    return launch_inc_epoch(epoch_dev, es, prof ? nullptr : gctl);
+    return GENCD_OK;
   };
 
   for (int64_t e = 0; status != GENCD_OK && e < p->max_epochs && k_live > 0; ++e) {
