@@ -1614,8 +1614,11 @@ __global__ __launch_bounds__(kBlock) void k_improve(IterArgs a) {
   }
 }
 
-// positions per first-stage workgroup of a global accept
-constexpr int64_t kAcceptChunk = 2048;
+// A global accept takes two stages from kAcceptTwo positions on (below, one
+// workgroup needs no longer than a second launch), of kAcceptChunk positions
+// per first-stage workgroup: two a thread.  336k positions: 2048 16.3 us, 512
+// 9.2, 256 7.7 but 0.4 more in the second stage and as long in a solve.
+constexpr int64_t kAcceptTwo = 2048, kAcceptChunk = 512;
 
 // With events, Propose is launched through the extension that stamps the
 // kernel's own dispatch with them.
@@ -1665,7 +1668,7 @@ static int launch_iteration_g(const IterArgs &a, int mode, int64_t block, unsign
   } else {
     if (a.accept_top > 0) {
       hipLaunchKernelGGL(k_accept_top, dim3(1), dim3(kTopThreads), 0, s, a);
-    } else if (nblocks_accept == 1 && block > kAcceptChunk) {
+    } else if (nblocks_accept == 1 && block > kAcceptTwo) {
       // one block over the whole window (Greedy): chunk winners, then the best
       const int64_t nc = (block + kAcceptChunk - 1) / kAcceptChunk;
       hipLaunchKernelGGL(k_accept, dim3(unsigned(nc < 4096 ? nc : 4096)), blk, 0, s, a,
