@@ -469,9 +469,15 @@ static int32_t team_group(int64_t nnz, int64_t k_live) {
 __global__ __launch_bounds__(kBlock) void k_mp_order(const int32_t *live, int64_t k_live, PermKey pk,
                                                      const int64_t *col_ptr, const float *c,
                                                      int4 *order) {
+  __shared__ uint16_t f[4 << kPermTableHalf];
+  const bool table = pk.half <= kPermTableHalf;
+  if (table) perm_table(pk, f, int(threadIdx.x), kBlock);
+  __syncthreads();
   for (int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x; p < k_live;
        p += int64_t(gridDim.x) * kBlock) {
-    const int32_t j = live[perm_apply(pk, uint64_t(p))];
+    const int64_t q = table ? int64_t(perm_apply_table(pk, f, uint32_t(p)))
+                            : int64_t(perm_apply(pk, uint64_t(p)));
+    const int32_t j = live[q];
     const int64_t b = col_ptr[j];
     order[p] = make_int4(int32_t(uint32_t(b)), j, int32_t(col_ptr[j + 1] - b),
                          __float_as_int(c[j]));
