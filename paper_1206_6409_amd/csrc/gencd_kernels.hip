@@ -2227,7 +2227,7 @@ __global__ __launch_bounds__(kBlock) void k_rho_scale(int64_t k, int64_t n, cons
 // walks the blocks one after the other and keeps its columns' sums in LDS.
 // Rows are sorted inside a column, so a block's entries are one range, found
 // once per estimate by k_rho_cut.  Both then stream X once: at 25 M nonzeros
-// (n = 25 000, 200 MB) 77 and 75 us, 2.6 TB/s of the 4.7 TB/s a large copy
+// (n = 25 000, 200 MB) 75 and 70 us, 2.8 TB/s of the 4.7 TB/s a large copy
 // reaches; a 20-step estimate 26.5 -> 3.5 ms.
 constexpr int kRhoRows = 19456;       // 152 KB of LDS
 constexpr int kRhoMaxBlocks = 3;      // cuts live in two arrays of k
@@ -2240,8 +2240,10 @@ struct RhoArgs {
   const float *val;
   const int32_t *live;    // non-empty columns
   int32_t *cut0, *cut1;   // [k] first entry (offset in its column) of row block 1, 2
+  int64_t *bound;         // [parts + 1] first live column of every chunk of spmv, then
+                          // [chunks + 1] of cols
   int64_t n, k_live, nnz;
-  int32_t nb, rows, parts, G;
+  int32_t nb, rows, parts, chunks;
 };
 
 __global__ __launch_bounds__(kBlock) void k_rho_cut(RhoArgs a) {
@@ -2265,7 +2267,8 @@ __global__ __launch_bounds__(kBlock) void k_rho_cut(RhoArgs a) {
 // below end): columns, entry ranges [lo, hi) of row block b, and the first
 // G * kUnroll entries of each.  Taken together, the loads of one stage of the
 // chain position -> column -> bounds -> entries are in flight at the same
-// time; one column after the other took 120 us instead of 77.
+// time; one column after the other took 120 us instead of 77.  (Loading the
+// next batch while working on this one, with two columns, changes nothing.)
 constexpr int kRhoCols = 4;
 struct RhoBatch {
   int32_t j[kRhoCols];
@@ -2289,19 +2292,23 @@ __device__ __forceinline__ void rho_load(const RhoArgs &a, int32_t b, int64_t q,
   }
 #pragma unroll
   for (int v = 0; v < kRhoCols; ++v) {
+    // byte offsets of 32 bits (launch_rho bounds the entries): the wave's
+    // instructions are the limit, and 64-bit addresses were a quarter of them
+    const uint32_t last = t.hi[v] > 0 ? t.hi[v] - 1 : 0;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const uint32_t e = t.lo[v] + uint32_t(u * G + lane);
-      const uint32_t at = e < t.hi[v] ? e : uint32_t(a.nnz - 1);
-      const int32_t r = a.row_idx[at];
-      t.vv[v][u] = a.val[at];
+      const uint32_t at = 4u * (e < last ? e : last);
+      const int32_t r =
+          *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(a.row_idx) + at);
+      t.vv[v][u] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.val) + at);
       t.ri[v][u] = e < t.hi[v] ? r : -1;
     }
   }
 }
 
 // First live column whose entries start at or after `target` (the chunks'
-// bounds): a search over 64 probes a round by the first wave.
+// bounds): a search over 64 probes a round by one wave.
 __device__ __forceinline__ int64_t rho_bound(const RhoArgs &a, int64_t target) {
   int64_t lo = 0, hi = a.k_live;  // the answer is in [lo, hi]
   while (hi > lo) {
@@ -2317,20 +2324,23 @@ __device__ __forceinline__ int64_t rho_bound(const RhoArgs &a, int64_t target) {
   return lo;
 }
 
+// The chunks' bounds, once per power iteration's 2 * iters products.
+__global__ __launch_bounds__(kWave) void k_rho_bounds(RhoArgs a) {
+  const int32_t i = int32_t(blockIdx.x), m = i <= a.parts ? a.parts : a.chunks;
+  const int32_t c = i <= a.parts ? i : i - a.parts - 1;
+  const int64_t v = c == m ? a.k_live : rho_bound(a, a.nnz * c / m);
+  if (threadIdx.x == 0) a.bound[i] = v;
+}
+
 template <int G>
 __global__ __launch_bounds__(kRhoThreads) void k_rho_spmv(RhoArgs a, const double *x,
                                                            double *part) {
   __shared__ double sl[kRhoRows];
-  __shared__ int64_t bound[2];
   const int32_t b = int32_t(blockIdx.x) % a.nb, c = int32_t(blockIdx.x) / a.nb;
   const int64_t r0 = int64_t(b) * a.rows;
   const int32_t m = int32_t(a.n - r0 < a.rows ? a.n - r0 : a.rows);
   for (int32_t i = threadIdx.x; i < m; i += kRhoThreads) sl[i] = 0.0;
-  if (threadIdx.x < 2 * kWave) {
-    const int w = int(threadIdx.x) / kWave;
-    const int64_t v = c + w == a.parts ? a.k_live : rho_bound(a, a.nnz * (c + w) / a.parts);
-    if ((threadIdx.x & (kWave - 1)) == 0) bound[w] = v;
-  }
+  const int64_t *const bound = a.bound + c;
   __syncthreads();
   const int lane = int(threadIdx.x) & (G - 1);
   constexpr int64_t NG = kRhoThreads / G;
@@ -2368,14 +2378,7 @@ template <int G>
 __global__ __launch_bounds__(kRhoThreads) void k_rho_cols(RhoArgs a, const double *s64, double *u) {
   __shared__ double sl[kRhoRows];
   __shared__ double acc[kRhoChunkCols];
-  __shared__ int64_t bound[2];
-  const int32_t c = blockIdx.x, nc = gridDim.x;
-  if (threadIdx.x < 2 * kWave) {
-    const int w = int(threadIdx.x) / kWave;
-    const int64_t v = c + w == nc ? a.k_live : rho_bound(a, a.nnz * (c + w) / nc);
-    if ((threadIdx.x & (kWave - 1)) == 0) bound[w] = v;
-  }
-  __syncthreads();
+  const int64_t *const bound = a.bound + a.parts + 1 + blockIdx.x;
   const int lane = int(threadIdx.x) & (G - 1);
   constexpr int64_t NG = kRhoThreads / G;
   const int64_t q1 = bound[1];
@@ -2422,8 +2425,7 @@ static void launch_rho_products(const RhoArgs &a, const double *x, double *part,
   hipLaunchKernelGGL(k_rho_spmv<G>, dim3(unsigned(a.parts * a.nb)), dim3(kRhoThreads), 0, s, a, x,
                      part);
   hipLaunchKernelGGL(k_rho_fold, dim3(grid_for(a.n)), dim3(kBlock), 0, s, a.n, a.parts, part, s64);
-  const unsigned cg = unsigned(a.nnz / 8192 < 1 ? 1 : (a.nnz / 8192 > 256 ? 256 : a.nnz / 8192));
-  hipLaunchKernelGGL(k_rho_cols<G>, dim3(cg), dim3(kRhoThreads), 0, s, a, s64, u);
+  hipLaunchKernelGGL(k_rho_cols<G>, dim3(unsigned(a.chunks)), dim3(kRhoThreads), 0, s, a, s64, u);
 }
 
 int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws &ws, int64_t k_live,
@@ -2455,11 +2457,17 @@ int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws 
   parts = std::min<int64_t>(parts, X->nnz / 8192);
   parts = std::min<int64_t>(parts, 256 / ra.nb);
   constexpr int64_t kRhoMinParts = 8;
-  const bool lds = ra.nb <= kRhoMaxBlocks && parts >= kRhoMinParts;
+  const bool lds = ra.nb <= kRhoMaxBlocks && parts >= kRhoMinParts && X->nnz < (int64_t(1) << 30);
   ra.parts = int32_t(parts);
   const double per = double(X->nnz) / double(k_live) / double(ra.nb);  // entries per range
   hipLaunchKernelGGL(k_rho_init, dim3(grid_for(nk)), dim3(kBlock), 0, s, X->k, X->n, ws.g64,
                      ws.rho_dinv, ws.rho_x, 1.0 / sqrt(double(k_live)), ws.z64, ws.rho_hist, iters);
+  ra.chunks = int32_t(std::max<int64_t>(1, std::min<int64_t>(X->nnz / 8192, 256)));
+  ra.bound = reinterpret_cast<int64_t *>(ws.scat);  // counters of the epochs
+  static_assert(256 + 1 + 256 + 1 <= kChkRep * 16, "the bounds fit");
+  if (lds)
+    hipLaunchKernelGGL(k_rho_bounds, dim3(unsigned(ra.parts + ra.chunks + 2)), dim3(kWave), 0, s,
+                       ra);
   if (lds && ra.nb > 1)
     hipLaunchKernelGGL(k_rho_cut, dim3(grid_for(k_live)), dim3(kBlock), 0, s, ra);
   for (int t = 0; t < iters; ++t) {
