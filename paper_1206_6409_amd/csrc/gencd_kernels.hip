@@ -548,6 +548,39 @@ __device__ __forceinline__ void pos_counts(int32_t j, const int32_t *all_soff,
   lc = all_loff[j + 1] - all_loff[j];
 }
 
+// Pieces [t0, t1) of the 64 positions base, base + 1, ... of a wave, as one
+// list: `a` is the first piece of a lane's position (t1 past the order's end),
+// `src` of its column in desc_all_l.  Lane q of a batch finds the position that
+// holds its piece by bisection of the 64 firsts.  One column after the other
+// took 38 us where all of 50k columns are long, this 7; colour classes of the
+// Lasso workload 61 -> 15 us.
+__device__ __forceinline__ void order_pieces(int32_t a, int32_t src, int32_t t0, int32_t t1,
+                                             int32_t base, int lane, const int4 *desc_all_l,
+                                             int4 *desc_l) {
+  for (int32_t q0 = t0; q0 < t1; q0 += kWave * kUnroll) {
+    int4 d[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int32_t q = q0 + u * kWave + lane;
+      int g = 0;  // the last position whose first piece is <= q: its piece, as
+                  // positions without pieces share their first with the next
+#pragma unroll
+      for (int bit = kWave / 2; bit > 0; bit >>= 1)
+        if (__shfl(a, g + bit) <= q) g += bit;
+      const int32_t at = __shfl(src, g) + (q - __shfl(a, g));
+      if (q < t1) {
+        d[u] = desc_all_l[at];
+        d[u].z = base + g;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int32_t q = q0 + u * kWave + lane;
+      if (q < t1) desc_l[q] = d[u];
+    }
+  }
+}
+
 // natural != 0: live columns in index order (cyclic rule).  The epoch
 // number is read from device memory so that a captured epoch replays.
 // One 16-byte gather per position (the live column's record) gives the
@@ -660,33 +693,9 @@ __global__ __launch_bounds__(kOrderTile) void k_order_tail(
       wbl[T] = a + n;
     }
   }
-  // The wave's pieces as one list: lane q of a batch finds the position that
-  // holds piece q by bisection of the 64 first pieces (one column after the
-  // other took 38 us where all of 50k columns are long, this 7).
   const int32_t t0 = __builtin_amdgcn_readfirstlane(a);
-  const int32_t t1 = t0 + __builtin_amdgcn_readlane(x, kWave - 1);
-  for (int32_t q0 = t0; q0 < t1; q0 += kWave * kUnroll) {
-    int4 d[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int32_t q = q0 + u * kWave + lane;
-      int g = 0;  // the last position whose first piece is <= q: its piece, as
-                  // positions without pieces share their first with the next
-#pragma unroll
-      for (int bit = kWave / 2; bit > 0; bit >>= 1)
-        if (__shfl(a, g + bit) <= q) g += bit;
-      const int32_t at = __shfl(src, g) + (q - __shfl(a, g));
-      if (q < t1) {
-        d[u] = desc_all_l[at];
-        d[u].z = b * kOrderTile + (tid - lane) + g;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int32_t q = q0 + u * kWave + lane;
-      if (q < t1) desc_l[q] = d[u];
-    }
-  }
+  order_pieces(a, src, t0, t0 + __builtin_amdgcn_readlane(x, kWave - 1),
+               b * kOrderTile + (tid - lane), lane, desc_all_l, desc_l);
 }
 
 __global__ void k_inc_epoch(int64_t *epoch, GridCtl *ctl) {
@@ -708,10 +717,8 @@ __global__ __launch_bounds__(kBlock) void k_list_counts(const int32_t *cols, int
 
 // Descriptors of the order: each position's static descriptor, re-tagged
 // with the position.  A thread takes a position; then the whole wave copies
-// the pieces of its long columns, one column at a time, so that a heavy
-// column's hundreds of pieces take a round or two of 64 x kUnroll loads
-// instead of a long serial loop on a few lanes.  The loop is uniform over
-// the wave (every lane runs the same bases).
+// the pieces of its long columns.  The loop is uniform over the wave (every
+// lane runs the same bases).
 __global__ __launch_bounds__(kBlock) void k_order_desc(const int32_t *col_of_pos, int64_t m,
                                                         const int32_t *loff,
                                                         const int32_t *all_soff,
@@ -724,13 +731,12 @@ __global__ __launch_bounds__(kBlock) void k_order_desc(const int32_t *col_of_pos
   for (int64_t base = int64_t(blockIdx.x) * kBlock + threadIdx.x - lane; base < m;
        base += stride) {
     const int64_t p = base + lane;
-    int32_t j = 0;
-    bool lng = false;
-    if (p < m && shorts_done) {  // every desc_s written: find the long positions
-      lng = loff[p + 1] > loff[p];
-      if (lng) j = col_of_pos[p];
+    const int32_t a = loff[p < m ? p : m], t1 = loff[base + kWave < m ? base + kWave : m];
+    int32_t src = 0;
+    if (p < m && shorts_done) {  // every desc_s written: only the long positions
+      if (loff[p + 1] > a) src = all_loff[col_of_pos[p]];
     } else if (p < m) {
-      j = col_of_pos[p];
+      const int32_t j = col_of_pos[p];
       const int32_t sj = all_soff[j];
       if (all_soff[j + 1] > sj) {  // short column
         int4 d = desc_all_s[sj];
@@ -738,33 +744,11 @@ __global__ __launch_bounds__(kBlock) void k_order_desc(const int32_t *col_of_pos
         desc_s[p] = d;
       } else {
         desc_s[p] = make_int4(0, j, int32_t(p), 0);  // long: length 0
-        lng = true;
+        src = all_loff[j];
       }
     }
-    unsigned long long left = __ballot(lng);
-    while (left) {
-      const int g = __builtin_ctzll(left);  // a lane whose position is long
-      left &= left - 1;
-      const int64_t pg = base + g;
-      const int32_t jg = __shfl(j, g);
-      const int32_t a = loff[pg], b = loff[pg + 1], src = all_loff[jg];
-      for (int32_t q0 = a; q0 < b; q0 += kWave * kUnroll) {
-        int4 d[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const int32_t q = q0 + u * kWave + lane;
-          if (q < b) d[u] = desc_all_l[src + (q - a)];
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const int32_t q = q0 + u * kWave + lane;
-          if (q < b) {
-            d[u].z = int32_t(pg);
-            desc_l[q] = d[u];
-          }
-        }
-      }
-    }
+    order_pieces(a, src, __builtin_amdgcn_readfirstlane(a), t1, int32_t(base), lane, desc_all_l,
+                 desc_l);
   }
 }
 
