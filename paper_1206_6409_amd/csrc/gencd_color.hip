@@ -550,7 +550,7 @@ __global__ __launch_bounds__(kBlock) void k_round_work(
 // whole column's wave then has its mex, chunks OR their bitmaps into the
 // column's global one, and the last of them (a ticket per column) takes the mex
 // from there.  Colours, lists, counters and bitmaps are agent-scope words; the
-// CSR arrays are only read.  A round is 15.5 us (whole call 53 -> 29.8 ms): the
+// CSR arrays are only read.  A round is 15 us (whole call 53 -> 28.7 ms): the
 // chain list -> entry -> row -> colours -> LDS counts (5 us), the bitmap's and
 // the ticket's round trips, the counters' atomics, the lists' and the barrier.
 // ---------------------------------------------------------------------------
@@ -561,6 +561,7 @@ constexpr int kCgWords = 256;      // bitmap words: up to 8192 colours
 constexpr int32_t kCgChunk = 16;   // entries of a chunk (64: 48 ms, 32: 36.0, 16: 32.4, 8: 35.4)
 constexpr int kCgCut = 1536;       // cut columns a round can hold
 constexpr int32_t kCgRounds = 4096;
+constexpr int kCgHash = 1024;      // counts a workgroup sums in LDS (2048: 29.3 ms, 1024: 28.7)
 constexpr int kCgSG = 16;          // lanes per entry
 constexpr int kCgPer = kWave / kCgSG;  // entries a wave walks at once ...
 constexpr int kCgDeep = 4;         // ... times this many groups of loads in flight
@@ -638,8 +639,8 @@ __device__ __forceinline__ void color_walk(const ColorGridArgs &a, int64_t e0, i
                                            int32_t *hcnt, int32_t *front, int nx, int par) {
   const int sub = lane / kCgSG, l = lane & (kCgSG - 1);
   auto later = [&](int32_t j2) {
-    uint32_t h = (uint32_t(j2) * 2654435761u) & (kHash - 1);
-    for (int p = 0; p < kProbe; ++p, h = (h + 1) & (kHash - 1)) {
+    uint32_t h = (uint32_t(j2) * 2654435761u) & (kCgHash - 1);
+    for (int p = 0; p < kProbe; ++p, h = (h + 1) & (kCgHash - 1)) {
       const int32_t prev = atomicCAS(&hkey[h], -1, j2);
       if (prev == -1 || prev == j2) {
         atomicAdd(&hcnt[h], 1);
@@ -719,7 +720,7 @@ __global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
   __shared__ int sm[2];
   __shared__ int32_t head[3];
   __shared__ uint32_t bitmap[kCgWaves][kCgWords];
-  __shared__ int32_t hkey[kHash], hcnt[kHash];
+  __shared__ int32_t hkey[kCgHash], hcnt[kCgHash];
   int members;
   const int me = __builtin_amdgcn_readfirstlane(grid_enroll(&a.ctl->g, int(gridDim.x), sm, members));
   members = __builtin_amdgcn_readfirstlane(members);
@@ -738,10 +739,17 @@ __global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
     const int cur = r % 3, nx = (r + 1) % 3, par = r & 1;
     int32_t *const front = par ? a.front_a : a.front_b;   // whole columns of this round
     int32_t *const next = par ? a.front_b : a.front_a;
+    // the first cut columns beside the counters that say how many there are
+    unsigned long long v = agent_load(&a.ctl->cut_list[par][lane]);
+    uint32_t vb = agent_load(&a.ctl->cut_beg[par][lane]);
     if (threadIdx.x < 3)
       head[threadIdx.x] = agent_load(threadIdx.x == 0   ? &a.ctl->whole[cur]
                                      : threadIdx.x == 1 ? &a.ctl->cut[cur]
                                                         : &a.ctl->round_max[cur]);
+    for (int u = threadIdx.x; u < kCgHash; u += kCgThreads) {
+      hkey[u] = -1;
+      hcnt[u] = 0;
+    }
     __syncthreads();
     const int32_t F = head[0], H = head[1] < kCgCut ? head[1] : kCgCut;
     maxc = head[2] > maxc ? head[2] : maxc;
@@ -762,11 +770,6 @@ __global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
     }
     colored += F + H;
     if (me < F || H > 0) {  // uniform over the workgroup
-      for (int u = threadIdx.x; u < kHash; u += kCgThreads) {
-        hkey[u] = -1;
-        hcnt[u] = 0;
-      }
-      __syncthreads();
       for (int32_t i = wave; i < F; i += nw) {
         const int32_t j = __builtin_amdgcn_readfirstlane(agent_load(&front[i]));
         for (int32_t u = lane; u < words; u += kWave) bits[u] = 0u;
@@ -781,9 +784,10 @@ __global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
       }
       int32_t seen = 0;  // chunks handed out so far, modulo the waves
       for (int32_t h0 = 0; h0 < H; h0 += kWave) {
-        const unsigned long long v =
-            h0 + lane < H ? agent_load(&a.ctl->cut_list[par][h0 + lane]) : 0ull;
-        const uint32_t vb = h0 + lane < H ? agent_load(&a.ctl->cut_beg[par][h0 + lane]) : 0u;
+        if (h0 > 0) {
+          v = h0 + lane < H ? agent_load(&a.ctl->cut_list[par][h0 + lane]) : 0ull;
+          vb = h0 + lane < H ? agent_load(&a.ctl->cut_beg[par][h0 + lane]) : 0u;
+        }
         const int nh = H - h0 < kWave ? H - h0 : kWave;
         for (int g = 0; g < nh; ++g) {
           const int32_t len = __builtin_amdgcn_readlane(int(v >> 32), g);
@@ -817,7 +821,7 @@ __global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
         }
       }
       __syncthreads();
-      for (int u = threadIdx.x; u < kHash; u += kCgThreads) {
+      for (int u = threadIdx.x; u < kCgHash; u += kCgThreads) {
         const int32_t key = hkey[u];
         if (key >= 0) {
           const int32_t c = hcnt[u];
