@@ -244,7 +244,7 @@ def main():
     log("timing Propose and Update launches (kernel events)")
     _, stats_prof, _ = run(G.SHOTGUN, max(args.steps // 2, 1), 1, flags=G.PROFILE, **tuned)
     dt, stats = dt_plain, stats_plain
-    path = "plain (per-iteration launches)"
+    path = "plain (no captured graph)"
     graph_info = None
     if not args.no_graph:
         log("timing Shotgun solves (captured epoch graphs)")
