@@ -17,10 +17,10 @@
 //     next round's frontier.
 // Each frontier column takes the mex of the colours in its row prefixes.
 // The rounds run on a resident grid (k_color_grid below).  Past its 8192
-// colours they are separate launches: a small frontier (the heavy columns come first and form long chains of
-// single-column rounds) spreads its row prefixes over the whole grid, into
-// a bitmap per frontier column in global memory; a large one takes one
-// workgroup per column with the bitmap in LDS.
+// colours they are separate launches: a small frontier (the heavy columns come
+// first and form long chains of single-column rounds) spreads its row prefixes
+// over the whole grid, into a bitmap per frontier column in global memory; a
+// large one takes one workgroup per column with the bitmap in LDS.
 #include <cstddef>
 #include <vector>
 

@@ -58,8 +58,15 @@ __device__ __forceinline__ int32_t block_excl_scan(int32_t v, int32_t &total) {
   return pre + x - v;
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_tiles(const int32_t *in, int64_t len,
-                                                        int32_t *part) {
+// Up to three scans of one length at once: blockIdx.y picks the arrays.
+struct ScanArgs {
+  const int32_t *in[3];
+  int32_t *out[3], *part[3];
+  int32_t *total;  // may be null: the three sums
+};
+
+__global__ __launch_bounds__(kBlock) void k_scan_tiles(ScanArgs a, int64_t len) {
+  const int32_t *const in = a.in[blockIdx.y];
   int64_t base = int64_t(blockIdx.x) * kScanTile + int64_t(threadIdx.x) * kScanItems;
   int32_t s = 0;
 #pragma unroll
@@ -67,10 +74,11 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(const int32_t *in, int64_
     if (base + u < len) s += in[base + u];
   int32_t tot;
   block_excl_scan(s, tot);
-  if (threadIdx.x == 0) part[blockIdx.x] = tot;
+  if (threadIdx.x == 0) a.part[blockIdx.y][blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_part(int32_t *part, int64_t nparts) {
+__global__ __launch_bounds__(kBlock) void k_scan_part(ScanArgs a, int64_t nparts) {
+  int32_t *const part = a.part[blockIdx.y];
   int32_t carry = 0;
   for (int64_t b0 = 0; b0 < nparts; b0 += kBlock) {
     int64_t i = b0 + threadIdx.x;
@@ -80,12 +88,15 @@ __global__ __launch_bounds__(kBlock) void k_scan_part(int32_t *part, int64_t npa
     if (i < nparts) part[i] = carry + ex;
     carry += tot;
   }
-  if (threadIdx.x == 0) part[nparts] = carry;
+  if (threadIdx.x == 0) {
+    part[nparts] = carry;
+    if (a.total) a.total[blockIdx.y] = carry;
+  }
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_apply(const int32_t *in, int64_t len,
-                                                        const int32_t *part, int64_t nparts,
-                                                        int32_t *out) {
+__global__ __launch_bounds__(kBlock) void k_scan_apply(ScanArgs a, int64_t len, int64_t nparts) {
+  const int32_t *const in = a.in[blockIdx.y], *const part = a.part[blockIdx.y];
+  int32_t *const out = a.out[blockIdx.y];
   int64_t base = int64_t(blockIdx.x) * kScanTile + int64_t(threadIdx.x) * kScanItems;
   int32_t v[kScanItems];
   int32_t s = 0;
@@ -104,20 +115,20 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const int32_t *in, int64_
   if (blockIdx.x == 0 && threadIdx.x == 0) out[len] = part[nparts];
 }
 
-int scan_exclusive(const int32_t *in, int32_t *out, int64_t len, int32_t *part, hipStream_t s) {
-  if (len <= 0) {
-    hipLaunchKernelGGL(k_scan_part, dim3(1), dim3(kBlock), 0, s, part, int64_t(0));
-    // out[0] = 0
-    hipLaunchKernelGGL(k_scan_apply, dim3(1), dim3(kBlock), 0, s, in, int64_t(0), part,
-                       int64_t(0), out);
-    return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
-  }
-  int64_t nparts = (len + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(k_scan_tiles, dim3(unsigned(nparts)), dim3(kBlock), 0, s, in, len, part);
-  hipLaunchKernelGGL(k_scan_part, dim3(1), dim3(kBlock), 0, s, part, nparts);
-  hipLaunchKernelGGL(k_scan_apply, dim3(unsigned(nparts)), dim3(kBlock), 0, s, in, len, part,
-                     nparts, out);
+static int scan_many(const ScanArgs &a, unsigned count, int64_t len, hipStream_t s) {
+  const int64_t nparts = len > 0 ? (len + kScanTile - 1) / kScanTile : 0;
+  const unsigned blocks = unsigned(nparts > 0 ? nparts : 1);
+  if (nparts > 0)
+    hipLaunchKernelGGL(k_scan_tiles, dim3(blocks, count), dim3(kBlock), 0, s, a, len);
+  hipLaunchKernelGGL(k_scan_part, dim3(1, count), dim3(kBlock), 0, s, a, nparts);
+  // an empty scan still writes out[0] = 0
+  hipLaunchKernelGGL(k_scan_apply, dim3(blocks, count), dim3(kBlock), 0, s, a, len > 0 ? len : 0,
+                     nparts);
   return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
+}
+
+int scan_exclusive(const int32_t *in, int32_t *out, int64_t len, int32_t *part, hipStream_t s) {
+  return scan_many(ScanArgs{{in}, {out}, {part}, nullptr}, 1, len, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -483,11 +494,15 @@ int launch_preprocess(const gencd_csc *X, int loss, int piece, int short_max, co
   hipLaunchKernelGGL(k_col_counts, dim3(grid_for(k)), dim3(kBlock), 0, s, X->col_ptr, k, piece,
                      short_max, w.tmp_cnt, w.tmp_cnt2, w.col_of_pos,
                      want_max ? reinterpret_cast<unsigned long long *>(w.red) + 11 : nullptr);
-  int st = scan_exclusive(w.tmp_cnt, w.all_soff, k, w.scan_part, s);
-  if (st) return st;
-  st = scan_exclusive(w.tmp_cnt2, w.all_loff, k, w.scan_part, s);
-  if (st) return st;
-  st = scan_exclusive(w.col_of_pos, w.soff, k, w.scan_part, s);  // live positions
+  // short columns, long pieces and live positions in three launches instead of
+  // nine (a check of a small matrix 246 -> 188 us); their partial sums need a
+  // 2048th of k, and the epochs' arrays are free by now.  The totals go to the
+  // reduction block, which is read back anyway.
+  const int st = scan_many(ScanArgs{{w.tmp_cnt, w.tmp_cnt2, w.col_of_pos},
+                                    {w.all_soff, w.all_loff, w.soff},
+                                    {w.scan_part, w.loff, w.wbl},
+                                    reinterpret_cast<int32_t *>(w.red + 13)},
+                           3, k, s);
   if (st) return st;
   hipLaunchKernelGGL(k_col_scatter, dim3(grid_for(k)), dim3(kBlock), 0, s, X->col_ptr, k, piece,
                      w.all_soff, w.all_loff, w.soff, w.desc_all_s, w.desc_all_l, w.live,

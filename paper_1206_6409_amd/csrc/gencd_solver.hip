@@ -216,18 +216,14 @@ int setup(const gencd_csc *X, const float *y, int loss, const gencd_params *p, v
   if (st) return st;
   st = launch_preprocess(X, loss, out->piece, smax, w, want_max, s);
   if (st) return st;
-  int32_t host[3] = {0, 0, 0};
   Red r{};
-  GENCD_HIP(hipMemcpyAsync(&host[0], w.all_soff + X->k, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  GENCD_HIP(hipMemcpyAsync(&host[1], w.soff + X->k, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  GENCD_HIP(hipMemcpyAsync(&host[2], w.all_loff + X->k, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   st = read_red(w, s, &r);
   if (st) return st;
   if (r.bad & 1ull) return GENCD_ERR_BAD_MATRIX;
   if (r.bad & 2ull) return GENCD_ERR_BAD_LABELS;
-  out->n_short = host[0];
-  out->k_live = host[1];
-  out->n_lpieces = host[2];
+  out->n_short = r.totals[0];
+  out->n_lpieces = r.totals[1];
+  out->k_live = r.totals[2];
   out->max_len = int64_t(r.max_len);
   st = launch_curvature(X, loss, out->n_short, out->n_lpieces, w, s);
   if (st) return st;

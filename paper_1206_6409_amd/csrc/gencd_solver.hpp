@@ -18,7 +18,9 @@ struct Red {
   double dual_sum;
   unsigned long long pad[2];
   unsigned long long acc_nnz, acc_cnt, bad, max_len;  // max_len: set by the set-up
-  unsigned long long pad2[4];
+  unsigned long long epoch;
+  int32_t totals[4];  // set by the set-up: short columns, long pieces, live columns
+  unsigned long long pad2;
 };
 static_assert(sizeof(Red) == 16 * 8, "reduction block layout");
 
