@@ -67,6 +67,8 @@ struct SoloOut {
   int64_t epoch, next_check;  // epochs run so far, and the next due check
   double objective, kkt, gap, drift, best;  // the last check; drift: the largest
   int64_t nnz_w, checked;     // checked: the launch ended on a check
+  double l1_empty;            // weights of the columns without entries: |w|_1 and
+  int64_t nz_empty;           // nonzeros (they never change)
 };
 
 struct SoloArgs {
@@ -83,6 +85,9 @@ struct SoloArgs {
   SoloOut *out;
   int64_t k, k_live;
   int32_t n, S, loss, natural, inner, build_rec;
+  int32_t sum_empty;          // find l1_empty and nz_empty in this launch
+  double l1_empty;
+  int64_t nz_empty;
   int32_t max_len;   // entries of the longest column
   float lam, n_f;
   double lam64, inv_n, kkt_tol, gap_tol, best;

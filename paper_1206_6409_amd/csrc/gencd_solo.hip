@@ -143,7 +143,9 @@ __device__ __forceinline__ void solo_scatter(int32_t base, int32_t len, int gl,
 }
 
 // FP64 check inside the workgroup (the quantities of k_check_*): z64 = Xw in
-// LDS, objective, KKT, gap, drift, and the re-sync of (z_hi, z_lo).
+// LDS, objective, KKT, gap, drift, and the re-sync of (z_hi, z_lo).  The
+// columns without entries come in through o: no step changes their weights,
+// and each nonzero one violates Eq. (1)'s conditions by lambda.
 template <int NT, int G>
 __device__ __forceinline__ void solo_check(const SoloArgs &a, double *z64, float *zh, float *zl, const float *yy,
                            double (*sm)[8], SoloOut &o) {
@@ -236,6 +238,9 @@ __device__ __forceinline__ void solo_check(const SoloArgs &a, double *z64, float
     }
   }
   block_fold<NT, 7, 4>(f, sm);
+  f[2] += o.l1_empty;
+  f[3] += double(o.nz_empty);
+  if (o.nz_empty > 0 && !(a.lam64 <= f[5])) f[5] = a.lam64;
   const double gm = f[6], sc = gm > a.lam64 ? a.lam64 / gm : 1.0;
   double du[1] = {0.0};
 #pragma unroll 1
@@ -293,6 +298,20 @@ __global__ __launch_bounds__(kSoloThreads) void k_solo(SoloArgs a) {
   __syncthreads();
   SoloOut o{};
   o.best = a.best;
+  o.l1_empty = a.l1_empty;
+  o.nz_empty = a.nz_empty;
+  if (a.sum_empty) {
+    double em[2] = {0.0, 0.0};
+    for (int64_t j = tid; j < a.k; j += NT)
+      if (a.col_ptr[j] == a.col_ptr[j + 1]) {
+        const double wj = fabs(double(a.w[j]));
+        em[0] += wj;
+        em[1] += wj != 0.0 ? 1.0 : 0.0;
+      }
+    block_fold<NT, 2, 2>(em, sm);
+    o.l1_empty = em[0];
+    o.nz_empty = int64_t(em[1]);
+  }
   int64_t e = a.e0, next_check = a.next_check, windows = 0;
   const int32_t S = a.S, kl = int32_t(a.k_live), T = (kl + S - 1) / S;
   const bool overflow = a.max_len > G * U;  // some column needs a second batch

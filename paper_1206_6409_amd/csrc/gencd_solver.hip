@@ -671,6 +671,8 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       !fused && !a.exact_accum && p->improve_steps == 0 && p->piece == 0 && p->group == 0 &&
       p->residual == 0;
   // a restart with half the window (divergence guard) keeps the choice
+  double l1_empty = 0.0;  // weights of empty columns, from the first of its launches
+  int64_t nz_empty = 0;
   const bool solo = solo_rule && X->n <= kSoloMaxRows && solo_plan(X->n, X->nnz, k_live, su.max_len, S).ok;
 
   // Mid-size windows: the windows of an epoch in one launch on a grid of
@@ -792,6 +794,9 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       sa.zs = ws.zs;
       sa.rec = ws.live_rec;  // not read by anything else in such a solve
       sa.build_rec = e == 0 ? 1 : 0;
+      sa.sum_empty = e == 0 && (p->flags & GENCD_WARM_START) && k_live < X->k ? 1 : 0;
+      sa.l1_empty = l1_empty;
+      sa.nz_empty = nz_empty;
       sa.desc = ws.desc_s;
       sa.z64 = ws.z64;
       sa.out = reinterpret_cast<SoloOut *>(ws.rrep);
@@ -821,6 +826,8 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       SoloOut so{};
       GENCD_HIP(hipMemcpyAsync(&so, sa.out, sizeof(so), hipMemcpyDeviceToHost, s));
       GENCD_HIP(hipStreamSynchronize(s));
+      l1_empty = so.l1_empty;
+      nz_empty = so.nz_empty;
       ran = so.epoch - e;
       if (ran < 1) return GENCD_ERR_HIP;  // cannot happen
       if (plan.inner) {
