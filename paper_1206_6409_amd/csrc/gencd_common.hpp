@@ -191,6 +191,11 @@ __device__ __forceinline__ float row_group_sum(float x) {
   return x;
 }
 
+// Maximum of two doubles that a NaN on either side wins.
+__device__ __forceinline__ double nan_max(double a, double b) {
+  return a != a || b <= a ? a : b;
+}
+
 // One step of a reduction inside a DPP row: the partner's double, combined.
 template <int CTRL, bool MAX>
 __device__ __forceinline__ double dpp_fold(double v) {
@@ -199,7 +204,7 @@ __device__ __forceinline__ double dpp_fold(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), CTRL, 0xF, 0xF, false);
   const double o = __longlong_as_double((long long)(((unsigned long long)unsigned(hi) << 32) |
                                                     unsigned(lo)));
-  if constexpr (MAX) return o <= v ? v : o;  // a NaN wins
+  if constexpr (MAX) return nan_max(v, o);
   return v + o;
 }
 

@@ -1940,7 +1940,7 @@ __global__ __launch_bounds__(kBlock) void k_check_rows(int64_t n, int loss, cons
     if (zs) {  // re-sync: z_hi + z_lo = z64 to about 2^-48 relative, and the label
       const float4 old = zs[i];
       const double dv = fabs((double(old.x) + double(old.y)) - t);
-      if (!(dv <= drift)) drift = dv;  // propagates NaN
+      drift = nan_max(drift, dv);
       sq += t * t;
       const float h = float(t);
       zs[i] = make_float4(h, float(t - double(h)), y[i], 0.0f);
@@ -1954,8 +1954,7 @@ __global__ __launch_bounds__(kBlock) void k_check_rows(int64_t n, int loss, cons
     if (threadIdx.x < off) {
       sred[threadIdx.x] += sred[threadIdx.x + off];
       ssq[threadIdx.x] += ssq[threadIdx.x + off];
-      const double o = sdr[threadIdx.x + off];
-      if (!(o <= sdr[threadIdx.x])) sdr[threadIdx.x] = o;
+      sdr[threadIdx.x] = nan_max(sdr[threadIdx.x], sdr[threadIdx.x + off]);
     }
     __syncthreads();
   }
@@ -2045,7 +2044,7 @@ __global__ __launch_bounds__(kBlock) void k_check_kkt(int64_t k, double *g64, co
       if (j >= k) break;
       const double g = gv[u] * inv_n;
       g64[j] = g;
-      if (!(fabs(g) <= gmax)) gmax = fabs(g);
+      gmax = nan_max(gmax, fabs(g));
       const double wj = wv[u];
       double v;
       if (wj != 0.0) {
@@ -2056,7 +2055,7 @@ __global__ __launch_bounds__(kBlock) void k_check_kkt(int64_t k, double *g64, co
         v = fabs(g) - lam;
         if (v < 0.0) v = 0.0;
       }
-      if (!(v <= vmax)) vmax = v;  // propagates NaN
+      vmax = nan_max(vmax, v);
     }
   }
   smax[threadIdx.x] = vmax;
@@ -2066,10 +2065,8 @@ __global__ __launch_bounds__(kBlock) void k_check_kkt(int64_t k, double *g64, co
   __syncthreads();
   for (int off = kBlock / 2; off > 0; off >>= 1) {
     if (threadIdx.x < off) {
-      double o = smax[threadIdx.x + off];
-      if (!(o <= smax[threadIdx.x])) smax[threadIdx.x] = o;
-      double o2 = sgm[threadIdx.x + off];
-      if (!(o2 <= sgm[threadIdx.x])) sgm[threadIdx.x] = o2;
+      smax[threadIdx.x] = nan_max(smax[threadIdx.x], smax[threadIdx.x + off]);
+      sgm[threadIdx.x] = nan_max(sgm[threadIdx.x], sgm[threadIdx.x + off]);
       sl1[threadIdx.x] += sl1[threadIdx.x + off];
       snz[threadIdx.x] += snz[threadIdx.x + off];
     }

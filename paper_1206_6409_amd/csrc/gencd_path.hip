@@ -705,7 +705,7 @@ __global__ __launch_bounds__(kBlock) void k_path_kkt(int64_t k, double *g64, con
       if (j >= k) break;
       const double g = gv[u] * inv_n;
       g64[j * B + s] = g;
-      if (!(fabs(g) <= gmax)) gmax = fabs(g);
+      gmax = nan_max(gmax, fabs(g));
       const double wj = double(wv[u]);
       double v;
       if (wj != 0.0) {
@@ -716,7 +716,7 @@ __global__ __launch_bounds__(kBlock) void k_path_kkt(int64_t k, double *g64, con
         v = fabs(g) - l;
         if (v < 0.0) v = 0.0;
       }
-      if (!(v <= vmax)) vmax = v;
+      vmax = nan_max(vmax, v);
     }
   }
   smax[threadIdx.x] = vmax;
@@ -728,8 +728,8 @@ __global__ __launch_bounds__(kBlock) void k_path_kkt(int64_t k, double *g64, con
     double m = 0.0, a1 = 0.0, gm = 0.0, z = 0.0;
     for (int g = 0; g < GPB; ++g) {
       const int t = g * B + threadIdx.x;
-      if (!(smax[t] <= m)) m = smax[t];
-      if (!(sgm[t] <= gm)) gm = sgm[t];
+      m = nan_max(m, smax[t]);
+      gm = nan_max(gm, sgm[t]);
       a1 += sl1[t];
       z += snz[t];
     }

@@ -80,7 +80,7 @@ __device__ __forceinline__ void block_fold(double (&v)[NV], double (*sm)[8]) {
       if (i < NS)
         r += o;
       else
-        r = o <= r ? r : o;
+        r = nan_max(r, o);
     }
     v[i] = i < NS ? row_fold<false>(r) : row_fold<true>(r);
   }
@@ -183,7 +183,7 @@ __device__ __forceinline__ void solo_check(const SoloArgs &a, double *z64, float
     const double t = z64[i], yi = double(yy[i]);
     f[0] += loss_f64(a.loss, yi, t);
     const double dv = fabs((double(zh[i]) + double(zl[i])) - t);
-    if (!(dv <= f[4])) f[4] = dv;
+    f[4] = nan_max(f[4], dv);
     f[1] += t * t;
     const float h = float(t);
     zh[i] = h;
@@ -223,7 +223,7 @@ __device__ __forceinline__ void solo_check(const SoloArgs &a, double *z64, float
     for (int u = 0; u < V; ++u) {
       const double g = group_sum<G>(s[u]) * a.inv_n;
       if (gl != 0 || d[u].z == 0) continue;
-      if (!(fabs(g) <= f[6])) f[6] = fabs(g);
+      f[6] = nan_max(f[6], fabs(g));
       const double w = double(wj[u]);
       double v;
       if (w != 0.0) {
@@ -234,13 +234,13 @@ __device__ __forceinline__ void solo_check(const SoloArgs &a, double *z64, float
         v = fabs(g) - a.lam64;
         if (v < 0.0) v = 0.0;
       }
-      if (!(v <= f[5])) f[5] = v;
+      f[5] = nan_max(f[5], v);
     }
   }
   block_fold<NT, 7, 4>(f, sm);
   f[2] += o.l1_empty;
   f[3] += double(o.nz_empty);
-  if (o.nz_empty > 0 && !(a.lam64 <= f[5])) f[5] = a.lam64;
+  if (o.nz_empty > 0) f[5] = nan_max(f[5], a.lam64);
   const double gm = f[6], sc = gm > a.lam64 ? a.lam64 / gm : 1.0;
   double du[1] = {0.0};
 #pragma unroll 1
@@ -263,7 +263,7 @@ __device__ __forceinline__ void solo_check(const SoloArgs &a, double *z64, float
   o.nnz_w = int64_t(f[3]);
   const double rms = sqrt(f[1] / double(n));
   const double dr = rms > 0.0 ? f[4] / rms : 0.0;
-  if (!(dr <= o.drift)) o.drift = dr;
+  o.drift = nan_max(o.drift, dr);
 }
 
 // One launch: epochs [a.e0, ...) until an FP64 check falls due that the host

@@ -1,6 +1,8 @@
 """The FP64 checks that a small solve runs in its own launch agree with the
 separate kernels' (an explicit schedule, and gencd_check) on weights of
-columns without entries."""
+columns without entries and on a NaN."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -35,3 +37,25 @@ def test_weights_of_empty_columns_count(count):
                       (st["gap"], chk.gap)):
         assert abs(got - want) <= 1e-12 * max(1.0, abs(want))
     assert abs(st["kkt_max"] - lam) <= 1e-12
+
+
+# the NaN's column decides the lane, the group and the round that meet it
+@pytest.mark.parametrize("at", [0, 1, 6, 17, 63, 200, 511, 799])
+def test_a_nan_gradient_is_not_optimal(at):
+    """A NaN entry: the column has no curvature and keeps its zero weight, so
+    everything but its gradient stays finite."""
+    P = synth.make_bernoulli_problem(300, 800, 0.05, synth.LOGISTIC, seed=4, support=10)
+    assert np.diff(P.col_ptr).min() > 0
+    X, y = G.Matrix.of(P), torch.as_tensor(P.y, device="cuda")
+    lam = 0.3 * G.lambda_max(X, y, P.loss)
+    X.val[int(P.col_ptr[at])] = float("nan")
+    for sched in ({}, dict(group=8, piece=256)):
+        res = G.solve(X, y, G.make_params(P.loss, lam, rule="shotgun", select_size=10, seed=9,
+                                          tol=1e-3, max_epochs=60, **sched))
+        assert res.status == G.NOT_CONVERGED, sched
+        assert math.isnan(res.stats["kkt_max"]) and math.isfinite(res.stats["objective"]), sched
+        assert math.isnan(G.check(X, y, P.loss, lam, res.w).kkt)
+        assert res.w[at].item() == 0.0
+    prm = G.make_params(P.loss, 0.0, rule="shotgun", select_size=10, seed=9, tol=1e-3, max_epochs=60)
+    for st in G.solve_path(X, y, prm, [2.0 * lam, lam], B=16).stats:
+        assert not st["converged"] and math.isnan(st["kkt_max"]) and math.isfinite(st["objective"])
