@@ -661,6 +661,9 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
     prof_bytes_pending = prof_ubytes_pending = 0.0;
     ev_used = 0;
   };
+  auto fold_drift = [&](double d) {
+    st_out->z_drift = std::isfinite(d) ? std::max(st_out->z_drift, d) : d;
+  };
   GraphHolder graph;
   int64_t graph_S = -1;
   // Small windows: whole epochs in one workgroup.  A caller who fixed the
@@ -835,6 +838,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
         ck = CheckOut{so.objective, so.kkt, so.gap, so.nnz_w, 0, 0, so.drift};
         next_check = so.next_check;
         best = so.best;
+        fold_drift(so.drift);  // of all its checks, also where it ended between two
       }
     } else if (use_graph) {
       if (graph_S != S) {
@@ -888,10 +892,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
         st = run_check(X, y, p->loss, p->lambda, w, su, true, s, &ck);
         if (st) return st;
       }
-      if (std::isfinite(ck.drift_rel))
-        st_out->z_drift = std::max(st_out->z_drift, ck.drift_rel);
-      else
-        st_out->z_drift = ck.drift_rel;
+      fold_drift(ck.drift_rel);
       if (mode == 2) {
         if (!evs.empty())
           prof_ubytes_pending += 24.0 * double(ck.acc_nnz - acc_nnz_seen) +

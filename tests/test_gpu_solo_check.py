@@ -1,6 +1,6 @@
 """The FP64 checks that a small solve runs in its own launch agree with the
 separate kernels' (an explicit schedule, and gencd_check) on weights of
-columns without entries and on a NaN."""
+columns without entries, on a NaN and on the drift of every check."""
 import math
 
 import numpy as np
@@ -59,3 +59,18 @@ def test_a_nan_gradient_is_not_optimal(at):
     prm = G.make_params(P.loss, 0.0, rule="shotgun", select_size=10, seed=9, tol=1e-3, max_epochs=60)
     for st in G.solve_path(X, y, prm, [2.0 * lam, lam], B=16).stats:
         assert not st["converged"] and math.isnan(st["kkt_max"]) and math.isfinite(st["objective"])
+
+
+def test_drift_of_checks_inside_earlier_launches():
+    """z_drift is the largest over all checks: a longer run of the same
+    iterates has at least the shorter one's.  16 epochs of 1000 windows fill a
+    launch, which thus ends between two checks; the longest run ends in a later
+    one, where the weights no longer move and nothing drifts."""
+    P = synth.make_bernoulli_problem(400, 1000, 0.01, synth.LOGISTIC, seed=5, support=10)
+    X, y = G.Matrix.of(P), torch.as_tensor(P.y, device="cuda")
+    lam = 0.3 * G.lambda_max(X, y, P.loss)
+    drift = [G.solve(X, y, G.make_params(P.loss, lam, rule="cyclic", tol=0.0, max_epochs=e,
+                                         check_every=3)).stats["z_drift"] for e in (3, 15, 399)]
+    # the FP64 product that the drift is measured from is summed in any order
+    assert 0.0 < drift[0] <= drift[1] * (1 + 1e-6)
+    assert drift[1] <= drift[2] * (1 + 1e-6)
