@@ -65,6 +65,7 @@ int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
 // (gencd_solo.hip).
 struct SoloOut {
   int64_t epoch, next_check;  // epochs run so far, and the next due check
+  int64_t window;             // windows of the next epoch that have run
   double objective, kkt, gap, drift, best;  // the last check; drift: the largest
   int64_t nnz_w, checked;     // checked: the launch ended on a check
   double l1_empty;            // weights of the columns without entries: |w|_1 and
@@ -92,7 +93,8 @@ struct SoloArgs {
   float lam, n_f;
   double lam64, inv_n, kkt_tol, gap_tol, best;
   uint64_t seed;
-  int64_t e0, max_epochs, next_check, check_every, max_windows;
+  int64_t e0, max_epochs, next_check, check_every;
+  int32_t t0, max_windows;    // first window of epoch e0; windows of this launch
 };
 
 struct SoloPlan {

@@ -266,10 +266,11 @@ __device__ __forceinline__ void solo_check(const SoloArgs &a, double *z64, float
   o.drift = nan_max(o.drift, dr);
 }
 
-// One launch: epochs [a.e0, ...) until an FP64 check falls due that the host
-// takes (a.inner == 0), or (a.inner) until a check that ends the solve, calls
-// for the divergence guard or is the last one, or until a.max_windows windows
-// have run.  G lanes per column, U entries per lane and batch; ONE: a window
+// One launch: from window a.t0 of epoch a.e0 on, until an FP64 check falls due
+// that the host takes (a.inner == 0), or (a.inner) until a check that ends the
+// solve, calls for the divergence guard or is the last one, or until
+// a.max_windows windows have run, where the next launch takes up the epoch.
+// G lanes per column, U entries per lane and batch; ONE: a window
 // fits one wave, the other waves only take part in the rest of the epoch.
 template <int G, int U, bool ONE>
 __global__ __launch_bounds__(kSoloThreads) void k_solo(SoloArgs a) {
@@ -312,17 +313,21 @@ __global__ __launch_bounds__(kSoloThreads) void k_solo(SoloArgs a) {
     o.l1_empty = em[0];
     o.nz_empty = int64_t(em[1]);
   }
-  int64_t e = a.e0, next_check = a.next_check, windows = 0;
+  int64_t e = a.e0, next_check = a.next_check;
   const int32_t S = a.S, kl = int32_t(a.k_live), T = (kl + S - 1) / S;
+  int32_t t0 = a.t0, left = a.max_windows;
   const bool overflow = a.max_len > G * U;  // some column needs a second batch
   for (;;) {
-    // Select: the epoch's order as one descriptor {first entry, column,
-    // length, curvature} per position
-    const PermKey pk = make_perm_key(a.k_live, a.seed, e);
+    if (t0 == 0) {
+      // Select: the epoch's order as one descriptor {first entry, column,
+      // length, curvature} per position
+      const PermKey pk = make_perm_key(a.k_live, a.seed, e);
 #pragma unroll 1
-    for (int64_t p = tid; p < a.k_live; p += NT)
-      a.desc[p] = a.rec[a.natural ? p : int64_t(perm_apply(pk, uint64_t(p)))];
-    __syncthreads();
+      for (int64_t p = tid; p < a.k_live; p += NT)
+        a.desc[p] = a.rec[a.natural ? p : int64_t(perm_apply(pk, uint64_t(p)))];
+      __syncthreads();
+    }
+    const int32_t t1 = T - t0 < left ? T : t0 + left;
     // position of this group in window t, or past the end
     auto desc_at = [&](int32_t t) {
       int4 d = make_int4(0, 0, 0, 0);
@@ -404,31 +409,36 @@ __global__ __launch_bounds__(kSoloThreads) void k_solo(SoloArgs a) {
     };
     if (!ONE || tid < kWave) {
       ColSlot<G, U> c0, c1, c2, c3;
-      c0.d = desc_at(0);
-      c1.d = desc_at(1);
-      c2.d = desc_at(2);
-      c3.d = desc_at(3);
+      c0.d = desc_at(t0);
+      c1.d = desc_at(t0 + 1);
+      c2.d = desc_at(t0 + 2);
+      c3.d = desc_at(t0 + 3);
       fetch(c0);
       fetch(c1);
 #pragma unroll 1
-      for (int32_t t = 0; t < T; t += 4) {
+      for (int32_t t = t0; t < t1; t += 4) {
         window(t, c0, c2);
-        if (t + 1 < T) window(t + 1, c1, c3);
-        if (t + 2 < T) window(t + 2, c2, c0);
-        if (t + 3 < T) window(t + 3, c3, c1);
+        if (t + 1 < t1) window(t + 1, c1, c3);
+        if (t + 2 < t1) window(t + 2, c2, c0);
+        if (t + 3 < t1) window(t + 3, c3, c1);
       }
     }
     __syncthreads();
+    left -= t1 - t0;
+    t0 = t1 < T ? t1 : 0;
+    if (t0 > 0) {  // inside the epoch; the FP32 pairs go through memory as they are
+      o.checked = 0;
+      break;
+    }
     for (int i = tid; i < a.n; i += NT) {  // exact renormalisation, as k_renorm
       const float h = zh[i], l = zl[i];
       zh[i] = h + l;
       zl[i] = twosum_err(h, l);
     }
     ++e;
-    windows += T;
     const bool due = e >= next_check || e == a.max_epochs;
     if (!a.inner) {
-      if (due || windows + T > a.max_windows) break;
+      if (due || left == 0) break;
       __syncthreads();
       continue;
     }
@@ -450,12 +460,13 @@ __global__ __launch_bounds__(kSoloThreads) void k_solo(SoloArgs a) {
       }
       __syncthreads();
     }
-    if (windows + T > a.max_windows) break;
+    if (left == 0) break;
   }
   __syncthreads();
   for (int i = tid; i < a.n; i += NT) a.zs[i] = make_float4(zh[i], zl[i], yy[i], 0.0f);
   if (tid == 0) {
     o.epoch = e;
+    o.window = t0;
     o.next_check = next_check;
     *a.out = o;
   }

@@ -487,9 +487,9 @@ bool wants_rs(const gencd_params *p, int64_t positions, int64_t nnz, int64_t k_l
   return double(positions) * double(nnz) / double(k_live) >= 4.0 * double(n);
 }
 
-// Windows of one single-workgroup launch (a few to a few tens of
-// milliseconds, so that other streams' work is not held up for long).
-constexpr int64_t kSoloMaxWindows = 16384;
+// Windows of one single-workgroup launch (0.6 to 5 us each, so 10 to 80 ms:
+// other streams' work is not held up for long).
+constexpr int32_t kSoloMaxWindows = 16384;
 
 // Windows for the resident grid: it is ahead of two launches per window up to
 // about 70k entries (61k 10.0 against 11.0 us, 80k 11.9 against 12.6, 122k
@@ -674,6 +674,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       !fused && !a.exact_accum && p->improve_steps == 0 && p->piece == 0 && p->group == 0 &&
       p->residual == 0;
   // a restart with half the window (divergence guard) keeps the choice
+  int64_t solo_window = 0;  // where its next launch takes up the epoch
   double l1_empty = 0.0;  // weights of empty columns, from the first of its launches
   int64_t nz_empty = 0;
   const bool solo = solo_rule && X->n <= kSoloMaxRows && solo_plan(X->n, X->nnz, k_live, su.max_len, S).ok;
@@ -796,8 +797,9 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       sa.w_ckpt = ws.w_ckpt;
       sa.zs = ws.zs;
       sa.rec = ws.live_rec;  // not read by anything else in such a solve
-      sa.build_rec = e == 0 ? 1 : 0;
-      sa.sum_empty = e == 0 && (p->flags & GENCD_WARM_START) && k_live < X->k ? 1 : 0;
+      const bool first = e == 0 && solo_window == 0;
+      sa.build_rec = first ? 1 : 0;
+      sa.sum_empty = first && (p->flags & GENCD_WARM_START) && k_live < X->k ? 1 : 0;
       sa.l1_empty = l1_empty;
       sa.nz_empty = nz_empty;
       sa.desc = ws.desc_s;
@@ -823,6 +825,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       sa.max_epochs = p->max_epochs;
       sa.next_check = next_check;
       sa.check_every = check_every;
+      sa.t0 = int32_t(solo_window);
       sa.max_windows = kSoloMaxWindows;
       st = launch_solo(sa, plan, s);
       if (st) return st;
@@ -832,13 +835,18 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       l1_empty = so.l1_empty;
       nz_empty = so.nz_empty;
       ran = so.epoch - e;
-      if (ran < 1) return GENCD_ERR_HIP;  // cannot happen
+      solo_window = so.window;
+      if (ran < 0 || (ran == 0 && so.window == 0)) return GENCD_ERR_HIP;  // cannot happen
       if (plan.inner) {
         checked = so.checked != 0;
         ck = CheckOut{so.objective, so.kkt, so.gap, so.nnz_w, 0, 0, so.drift};
         next_check = so.next_check;
         best = so.best;
         fold_drift(so.drift);  // of all its checks, also where it ended between two
+      }
+      if (ran == 0) {  // inside its first epoch
+        --e;
+        continue;
       }
     } else if (use_graph) {
       if (graph_S != S) {
