@@ -175,11 +175,12 @@ __device__ __forceinline__ float split_total(const float *part, int32_t pf, int3
   return rows_sum(row_group_sum<16>(t));
 }
 
-// MODE 0: Jacobi windows, atomic scatter.  MODE 1: Coloring (rows of a window
+// Windows [t0, T) of an epoch.  MODE 0: Jacobi windows, atomic scatter.  MODE 1: Coloring (rows of a window
 // disjoint): compensated stores.
 template <int GS, int MODE>
 __global__ __launch_bounds__(kGridThreads) void k_epoch_grid(IterArgs a, GridCtl *ctl,
-                                                        unsigned long long *bad, int32_t T) {
+                                                             unsigned long long *bad, int32_t t0,
+                                                             int32_t T) {
   __shared__ int sm[2];
   int members;
   const int me = __builtin_amdgcn_readfirstlane(grid_enroll(ctl, int(gridDim.x), sm, members));
@@ -189,10 +190,10 @@ __global__ __launch_bounds__(kGridThreads) void k_epoch_grid(IterArgs a, GridCtl
   const int lane = int(threadIdx.x) & (kWave - 1);
   const int slot = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
   GridWave<GS> gw{a, slot * members + me, members * (kGridThreads / kWave), lane, 0, 0, 0};
-  gw.bounds(0, T);
+  gw.bounds(t0, T);
   const Rows z{__builtin_amdgcn_make_buffer_rsrc(a.zs, 0, int(a.nrows * 16), 0x00027000)};
   Unit cur[kUnits], nxt[kUnits];
-  WindowPos wp = gw.window(0, T), wn = gw.window(1, T);
+  WindowPos wp = gw.window(t0, T), wn = gw.window(t0 + 1, T);
 #pragma unroll
   for (int k = 0; k < kUnits; ++k) {
     const int32_t u = gw.wave + k * gw.nw;
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(kGridThreads) void k_epoch_grid(IterArgs a, GridCtl
 #pragma unroll
   for (int k = 0; k < kUnits; ++k) gw.fill(gw.is_long(wp, gw.wave + k * gw.nw), cur[k]);
   int round = 0;
-  for (int32_t t = 0; t < T; ++t) {
+  for (int32_t t = t0; t < T; ++t) {
     const WindowPos w2 = gw.window(t + 2, T);
     const int32_t nu = gw.units(wp);
     if (nu == 0) {  // an empty colour class: the same decision in every workgroup
@@ -409,8 +410,8 @@ constexpr int kSplits = 4;
 
 template <int GS>
 __global__ __launch_bounds__(kGridThreads) void k_greedy_grid(IterArgs a, GridCtl *ctl,
-                                                               unsigned long long *bad, int32_t T,
-                                                               int32_t B) {
+                                                              unsigned long long *bad, int32_t t0,
+                                                              int32_t T, int32_t B) {
   __shared__ int sm[2];
   __shared__ int smb[2];
   int members;
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(kGridThreads) void k_greedy_grid(IterArgs a, GridCt
   const int lane = int(threadIdx.x) & (kWave - 1);
   const int slot = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
   GridWave<GS> gw{a, slot * members + me, members * (kGridThreads / kWave), lane, 0, 0, 0};
-  gw.bounds(0, T);
+  gw.bounds(t0, T);
   const Rows z{__builtin_amdgcn_make_buffer_rsrc(a.zs, 0, int(a.nrows * 16), 0x00027000)};
   // {phi, delta} of a window slot in one word (delta and phi are adjacent
   // arrays of k); the published winners {first entry, length}, {0, delta} in the
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(kGridThreads) void k_greedy_grid(IterArgs a, GridCt
   auto word = [](uint32_t hi, float d) {
     return static_cast<unsigned long long>(hi) << 32 | __float_as_uint(d);
   };
-  WindowPos wp = gw.window(0, T), wn = gw.window(1, T);
+  WindowPos wp = gw.window(t0, T), wn = gw.window(t0 + 1, T);
   Unit cur, nxt;
   cur.d = gw.wave < gw.units(wp) ? gw.desc(wp, gw.wave) : make_int4(0, 0, 0, 0);
   nxt.d = gw.wave < gw.units(wn) ? gw.desc(wn, gw.wave) : make_int4(0, 0, 0, 0);
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(kGridThreads) void k_greedy_grid(IterArgs a, GridCt
   };
   AcceptPos at{}, atn{};
   accept_desc(accept_pos(wp), at);
-  for (int32_t t = 0; t < T; ++t) {
+  for (int32_t t = t0; t < T; ++t) {
     const WindowPos w2 = gw.window(t + 2, T);
     const int32_t nu = gw.units(wp);
     const uint32_t mark = uint32_t(t + 1) & 0xFFFFu;
@@ -661,12 +662,19 @@ static unsigned grid_size(double nnz) { return nnz <= 8192.0 ? 32 : 64; }
 
 template <int GS>
 static void launch_grid_g(const IterArgs &a, int mode, GridCtl *ctl, unsigned long long *bad,
-                          int32_t T, unsigned m, hipStream_t s) {
-  if (mode == 1)
-    hipLaunchKernelGGL((k_epoch_grid<GS, 1>), dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, T);
+                          int32_t t0, int32_t T, int32_t block, unsigned m, hipStream_t s) {
+  if (mode == 2)
+    hipLaunchKernelGGL(k_greedy_grid<GS>, dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, t0, T,
+                       block);
+  else if (mode == 1)
+    hipLaunchKernelGGL((k_epoch_grid<GS, 1>), dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, t0, T);
   else
-    hipLaunchKernelGGL((k_epoch_grid<GS, 0>), dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, T);
+    hipLaunchKernelGGL((k_epoch_grid<GS, 0>), dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, t0, T);
 }
+
+// Windows of one launch (5 to 20 us each, so at most about 80 ms: other
+// streams' work is not held up for long).
+constexpr int64_t kGridMaxWindows = 4096;
 
 int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
                       unsigned long long *bad, int64_t T, double nnz, int64_t block, hipStream_t s) {
@@ -675,24 +683,19 @@ int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
   if (a.piece > kWave * kUnroll || T < 1 || a.k_live < 1 || a.nrows * 16 > INT32_MAX)
     return GENCD_ERR_INVALID_ARG;
   const unsigned m = grid_size(nnz);
-  if (mode == 2) {
-    const auto tg = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3(m), dim3(kGridThreads), 0, s, a, ctl, bad, int32_t(T),
-                         int32_t(block));
-    };
-    switch (group) {
-      case 4: tg(k_greedy_grid<4>); break;
-      case 8: tg(k_greedy_grid<8>); break;
-      case 16: tg(k_greedy_grid<16>); break;
-      default: tg(k_greedy_grid<32>); break;
+  for (int64_t t0 = 0; t0 < T; t0 += kGridMaxWindows) {
+    if (t0 > 0) {  // the next launch's grid enrols anew
+      const int st = fill_i32(reinterpret_cast<int32_t *>(ctl), sizeof(GridCtl) / sizeof(int32_t), 0, s);
+      if (st) return st;
     }
-    return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
-  }
-  switch (group) {
-    case 4: launch_grid_g<4>(a, mode, ctl, bad, int32_t(T), m, s); break;
-    case 8: launch_grid_g<8>(a, mode, ctl, bad, int32_t(T), m, s); break;
-    case 16: launch_grid_g<16>(a, mode, ctl, bad, int32_t(T), m, s); break;
-    default: launch_grid_g<32>(a, mode, ctl, bad, int32_t(T), m, s); break;
+    const int32_t b = int32_t(t0), e = int32_t(std::min(T, t0 + kGridMaxWindows));
+    const int32_t blk = int32_t(block);
+    switch (group) {
+      case 4: launch_grid_g<4>(a, mode, ctl, bad, b, e, blk, m, s); break;
+      case 8: launch_grid_g<8>(a, mode, ctl, bad, b, e, blk, m, s); break;
+      case 16: launch_grid_g<16>(a, mode, ctl, bad, b, e, blk, m, s); break;
+      default: launch_grid_g<32>(a, mode, ctl, bad, b, e, blk, m, s); break;
+    }
   }
   return hipGetLastError() == hipSuccess ? GENCD_OK : GENCD_ERR_HIP;
 }

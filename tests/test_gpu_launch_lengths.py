@@ -20,8 +20,11 @@ def _kernels(fn):
 
 
 # (rows, rule, |J|, kernel, windows of an epoch, most windows of a launch).
+# One workgroup below 13312 rows, the resident grid above.
 @pytest.mark.parametrize("n,rule,S,kernel,limit", [
     (300, "cyclic", 1, "k_solo", 16384),
+    (14000, "cyclic", 1, "k_epoch_grid", 4096),
+    (14000, "thread_greedy", 2, "k_greedy_grid", 4096),
 ])
 def test_long_epochs_are_cut(n, rule, S, kernel, limit):
     P = synth.make_bernoulli_problem(n, 40000, 3.0 / n, synth.LOGISTIC, seed=2, support=10)
