@@ -29,6 +29,16 @@
 // once, so a device busy with other work gives a smaller grid, never a wait
 // for a workgroup that is not running.  Every wait is bounded; a wait that
 // runs out raises an error flag that the host reads with the next check.
+//
+// Beside other work an epoch waits for room once, the separate launches 2 T
+// times, but a workgroup of 1024 threads needs more room than theirs of 256.
+// Two launches -> this, ms a solve: beside a stream of 8192^3 bf16 products
+// |J| = 5000 of 10 entries 480 -> 31, |J| = 200 1615 -> 29; beside FP64
+// elementwise work 21.6 -> 26 and 53 -> 18; beside long-running workgroups that
+// leave 7 waves free on every CU (sums of 1600 long rows) 10.5 -> 50 and
+// 28.6 -> 15.5.  A lower bound on the members with a way back to the launches
+// gains up to a factor of two in the last kind of case only (17 -> 11 beside
+// 1400 rows) and would lose an order of magnitude in the first.
 #include <algorithm>
 
 #include "gencd_gridsync.hpp"
