@@ -483,6 +483,15 @@ constexpr int64_t kSoloInnerNnz = 131072;
 // 4.9 us, 8k 9.7 us) against 10 to 11 us for two launches at any size up to
 // this, so the line is drawn well below where they meet.
 constexpr int64_t kSoloWindowNnz = 4096;
+// Columns of a window, in lanes: one and a half rounds of the workgroup's lane
+// groups.  A further round is a chain of its own, while the resident grid
+// (gencd_grid.hip) takes the window in one.  2 M entries, n = 13 000, an epoch's
+// ms here / there: columns of 3, |J| = 192 10 / 14, 288 11 / 10, 512 9.3 / 6.0
+// (two launches 9.3), 1024 8.9 / 3.3 (4.7); of 24, 128 3.5 / 3.7, 160 4.4 / 3.1;
+// of 80, 32 4.3 / 4.3, 48 4.3 / 3.0 (4.2).  On a small matrix the checks and
+// orders between the launches weigh more: with 50 000 entries the two meet near
+// |J| = 300, with 16 000 near 600 (columns of 3).
+constexpr double kSoloLanes = 1536.0, kSoloLanesNnz = 81920.0;
 
 SoloPlan solo_plan(int64_t n, int64_t nnz, int64_t k_live, int64_t max_len, int64_t S) {
   SoloPlan p{};
@@ -490,12 +499,14 @@ SoloPlan solo_plan(int64_t n, int64_t nnz, int64_t k_live, int64_t max_len, int6
   if (k_live > (1 << 24) || nnz > (1 << 28)) return p;  // 32-bit positions and byte offsets
   const double mean = double(nnz) / double(k_live);
   if (double(S) * mean > double(kSoloWindowNnz)) return p;
+  const int wide = mean > 64.0 ? 64 : mean > 32.0 ? 16 : 8;  // lanes a column keeps busy
+  if (double(S) * wide > kSoloLanes * std::fmax(1.0, kSoloLanesNnz / double(nnz))) return p;
   if (mean > 64.0) {
     p.G = 64;
   } else if (S <= 4) {
     p.G = 16;  // one wave
   } else {
-    p.G = mean > 32.0 ? 16 : S * 8 <= kSoloThreads ? 8 : 4;
+    p.G = wide == 16 ? 16 : S * 8 <= kSoloThreads ? 8 : 4;
   }
   p.one = S * p.G <= kWave;
   p.U = p.G == 64 ? 4 : max_len <= p.G ? 1 : max_len <= 2 * p.G ? 2 : max_len <= 4 * p.G ? 4 : 6;

@@ -1,0 +1,40 @@
+"""Calls whose sizes are far from a kernel's best case take the form that is
+faster there.  Times are minima over a few calls on an otherwise idle device,
+compared with a call whose form is fixed; the factors leave room for noise and
+lie far below what the wrong form costs."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1206_6409_amd import gencd as G
+from paper_1206_6409_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _best(fn, reps=5):
+    fn()
+    best = float("inf")
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        fn()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+@pytest.mark.parametrize("k,mean,S", [(100_000, 5, 800), (200_000, 2, 1000), (5_000, 200, 20)])
+def test_many_columns_in_a_small_window(k, mean, S):
+    """Windows of at most 4096 entries in more columns than one workgroup has
+    lane groups: 2.5 and 3 times the resident grid's time in one workgroup
+    (which an explicit schedule rules out)."""
+    P = synth.make_bernoulli_problem(13_000, k, mean / 13_000, synth.LOGISTIC, seed=1, support=50)
+    X, y = G.Matrix.of(P), torch.as_tensor(P.y, device="cuda")
+    lam = 0.1 * G.lambda_max(X, y, P.loss)
+    kw = dict(rule="shotgun", select_size=S, seed=3, tol=0.0, max_epochs=2, check_every=2)
+    a, b = (_best(lambda: G.solve(X, y, G.make_params(P.loss, lam, **kw, **sched)))
+            for sched in ({}, dict(group=8, piece=256)))
+    assert a <= 1.5 * b, (a, b)
