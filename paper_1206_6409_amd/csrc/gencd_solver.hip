@@ -545,8 +545,10 @@ int path_setup(const gencd_csc *X, const float *y, const gencd_params *p, void *
 // ---------------------------------------------------------------------------
 // Solve
 // ---------------------------------------------------------------------------
+// ran_solo (may be null): whether the epochs run in one workgroup.
 int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float *w, float *z,
-               void *ws_base, size_t ws_bytes, hipStream_t s, gencd_stats *stats) {
+               void *ws_base, size_t ws_bytes, hipStream_t s, gencd_stats *stats,
+               bool *ran_solo = nullptr) {
   (void)hipGetLastError();  // launch checks below must not see an earlier error
   auto t0 = std::chrono::steady_clock::now();
   gencd_stats loc{};
@@ -678,6 +680,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
   double l1_empty = 0.0;  // weights of empty columns, from the first of its launches
   int64_t nz_empty = 0;
   const bool solo = solo_rule && X->n <= kSoloMaxRows && solo_plan(X->n, X->nnz, k_live, su.max_len, S).ok;
+  if (ran_solo) *ran_solo = solo;
 
   // Mid-size windows: the windows of an epoch in one launch on a grid of
   // resident workgroups.

@@ -2,6 +2,7 @@
 faster there.  Times are minima over a few calls on an otherwise idle device,
 compared with a call whose form is fixed; the factors leave room for noise and
 lie far below what the wrong form costs."""
+import json
 import time
 
 import numpy as np
@@ -38,3 +39,28 @@ def test_many_columns_in_a_small_window(k, mean, S):
     a, b = (_best(lambda: G.solve(X, y, G.make_params(P.loss, lam, **kw, **sched)))
             for sched in ({}, dict(group=8, piece=256)))
     assert a <= 1.5 * b, (a, b)
+
+
+def test_tuner_keeps_defaults_that_no_schedule_reaches(tmp_path):
+    """A small solve runs whole epochs in one workgroup with the defaults only,
+    several times faster than any explicit schedule."""
+    P = synth.c1_ccd_logistic(scale=0.3)
+    X, y = G.Matrix.of(P), torch.as_tensor(P.y, device="cuda")
+    prm = G.make_params(P.loss, 0.1 * G.lambda_max(X, y, P.loss), rule="shotgun", select_size=64,
+                        seed=2, tol=1e-6, max_epochs=2000)
+    cache = tmp_path / "tune.jsonl"
+    form = ("group", "piece", "residual", "flags")
+    s1 = G.autotune(X, y, prm, epochs=3, cache_path=str(cache))
+    assert s1["from_cache"] == 0 and all(s1[f] == 0 for f in form)
+    s2 = G.autotune(X, y, prm, epochs=3, cache_path=str(cache))
+    assert s2["from_cache"] == 1 and all(s2[f] == 0 for f in form)
+    tuned = G.apply_schedule(G.Params.from_buffer_copy(prm), s1)
+    a, b = (_best(lambda: G.solve(X, y, p)) for p in (tuned, prm))
+    assert a <= 1.5 * b, (a, b)
+    # a schedule timed on other kernels (a key without this version) is not taken
+    line = json.loads(cache.read_text())
+    version, key = line["key"].split("|", 1)
+    assert version[0] == "v" and version[1:].isdigit()
+    old = tmp_path / "old.jsonl"
+    old.write_text(json.dumps(dict(line, key=key, group=4, piece=128, residual=1)) + "\n")
+    assert G.autotune(X, y, prm, epochs=3, cache_path=str(old))["from_cache"] == 0
