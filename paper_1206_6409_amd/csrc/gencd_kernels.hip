@@ -393,7 +393,8 @@ __global__ __launch_bounds__(kBlock) void k_col_counts(const int64_t *col_ptr, i
     if ((unsigned long long)m > longest) longest = (unsigned long long)m;
   }
   if (!max_len) return;
-  // longest column: one atomic per workgroup (they queue on one address)
+  // longest column: one atomic per workgroup that has not seen a longer one
+  // (they queue on one address)
   __shared__ unsigned long long wl[kBlock / kWave];
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) {
@@ -404,7 +405,8 @@ __global__ __launch_bounds__(kBlock) void k_col_counts(const int64_t *col_ptr, i
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < kBlock / kWave; ++w) longest = wl[w] > longest ? wl[w] : longest;
-    atomicMax(max_len, longest);
+    if (longest > __hip_atomic_load(max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(max_len, longest);
   }
 }
 
@@ -2425,7 +2427,7 @@ static void launch_rho_products(const RhoArgs &a, const double *x, double *part,
 }
 
 int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws &ws, int64_t k_live,
-               int iters, hipStream_t s) {
+               int64_t max_len, int iters, hipStream_t s) {
   if (!ws.rho_dinv || iters < 1 || iters > kRhoMaxIters || k_live <= 0) return GENCD_ERR_INVALID_ARG;
   const int64_t nk = X->n > X->k ? X->n : X->k;
   unsigned blocks;
@@ -2453,9 +2455,30 @@ int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws 
   parts = std::min<int64_t>(parts, X->nnz / 8192);
   parts = std::min<int64_t>(parts, 256 / ra.nb);
   constexpr int64_t kRhoMinParts = 8;
-  const bool lds = ra.nb <= kRhoMaxBlocks && parts >= kRhoMinParts && X->nnz < (int64_t(1) << 30);
   ra.parts = int32_t(parts);
-  const double per = double(X->nnz) / double(k_live) / double(ra.nb);  // entries per range
+  // Entries per range (a column's share of a row block), and the lanes that
+  // take one.  Ranges cost 85 ns a thousand, entries 50 ns a thousand on the
+  // atomics: 1 M columns in two blocks of 1.0 entries a range 20 steps 3.5 ms
+  // (atomics 2.5), of 1.6 3.4 (4.0); in three of 0.6 5.1 (2.5), of 1.1 5.0 (4.0).
+  const double per = double(X->nnz) / double(k_live) / double(ra.nb);
+  const int lanes = per > 96.0 ? 64 : per > 24.0 ? 16 : 4;
+  constexpr double kRhoMinPer = 1.5;
+  // A group of lanes walks its columns alone, about 0.1 us per `lanes` entries,
+  // twice a step.  One column of H entries among 2 M others in columns of 10:
+  // H = 200 1.5 ms, 1000 2.2, 5000 5.8, 20 000 18.8 (atomics 2.4); in columns of
+  // 50, H = 1000 1.7, 5000 2.9, 20 000 7.6 (2.5); of 400, H = 5000 1.8, 20 000 3.3
+  // (2.2); among 20 M in columns of 10, H = 5000 10.3, 20 000 23.9 (20.4).  Text-like
+  // columns (5 M entries, n = 20 000) 17.8 (1.25).
+  const bool even = double(max_len) <= 1e-4 * double(X->nnz) * lanes;
+  // A workgroup of either product takes about 0.6 ns an entry, the atomics
+  // 0.05, less where a column's rows share cache lines.  n = 19 000: 1000 columns
+  // of 2000 entries (9 parts) 2.3 ms (1.7), 3000 (23 parts) 2.3 (5.2); of 15 000
+  // entries, 300 columns (19 parts) 3.8 (1.4), 1000 (65 parts) 3.9 (3.4).
+  const double density = double(X->nnz) / double(k_live) / double(X->n);
+  const bool wide = 0.6 * (1.0 / double(std::max<int64_t>(parts * ra.nb, 1)) + 1.0 / 256.0) <=
+                    0.05 / (1.0 + 5.0 * density);
+  const bool lds = ra.nb <= kRhoMaxBlocks && parts >= kRhoMinParts && X->nnz < (int64_t(1) << 30) &&
+                   per >= kRhoMinPer && even && wide;
   hipLaunchKernelGGL(k_rho_init, dim3(grid_for(nk)), dim3(kBlock), 0, s, X->k, X->n, ws.g64,
                      ws.rho_dinv, ws.rho_x, 1.0 / sqrt(double(k_live)), ws.z64, ws.rho_hist, iters);
   ra.chunks = int32_t(std::max<int64_t>(1, std::min<int64_t>(X->nnz / 8192, 256)));
@@ -2468,9 +2491,9 @@ int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws 
     hipLaunchKernelGGL(k_rho_cut, dim3(grid_for(k_live)), dim3(kBlock), 0, s, ra);
   for (int t = 0; t < iters; ++t) {
     if (lds) {
-      if (per > 96.0)
+      if (lanes == 64)
         launch_rho_products<64>(ra, ws.rho_x, part, ws.z64, ws.g64, s);
-      else if (per > 24.0)
+      else if (lanes == 16)
         launch_rho_products<16>(ra, ws.rho_x, part, ws.z64, ws.g64, s);
       else
         launch_rho_products<4>(ra, ws.rho_x, part, ws.z64, ws.g64, s);

@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle as O
 from paper_1206_6409_amd import gencd as G
 from paper_1206_6409_amd import synth
 
@@ -64,3 +65,61 @@ def test_tuner_keeps_defaults_that_no_schedule_reaches(tmp_path):
     old = tmp_path / "old.jsonl"
     old.write_text(json.dumps(dict(line, key=key, group=4, piece=128, residual=1)) + "\n")
     assert G.autotune(X, y, prm, epochs=3, cache_path=str(old))["from_cache"] == 0
+
+
+def _rho_kernels(X, iters=6):
+    from torch.profiler import ProfilerActivity, profile
+    G.estimate_rho(X, 2)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        est = G.estimate_rho(X, iters)
+        torch.cuda.synchronize()
+    return est, {e.name for e in prof.events()}
+
+
+def _with_column(P, at, rows):
+    """P with column `at` replaced by the given rows."""
+    a, b = int(P.col_ptr[at]), int(P.col_ptr[at + 1])
+    col_ptr = P.col_ptr.copy()
+    col_ptr[at + 1:] += rows.size - (b - a)
+    vals = np.random.default_rng(7).standard_normal(rows.size).astype(np.float32)
+    return synth.Problem(P.n, P.k, col_ptr,
+                         np.concatenate([P.row_idx[:a], rows.astype(P.row_idx.dtype), P.row_idx[b:]]),
+                         np.concatenate([P.val[:a], vals, P.val[b:]]), P.y, P.loss)
+
+
+# (rows, columns, mean entries, a column of this many entries, whether the row
+# vector is in LDS): one, two and three row blocks at their edges, every lane
+# group, and what rules the form out: a long column, short ranges, few partial
+# vectors, too many rows
+RHO = [
+    (19456, 50_000, 10, 0, True), (19457, 50_000, 10, 0, True), (38912, 90_000, 12, 0, True),
+    (38913, 90_000, 12, 0, True), (58368, 200_000, 12, 0, True), (58369, 200_000, 12, 0, False),
+    (3000, 6000, 40, 0, True), (3000, 3000, 150, 0, True), (19456, 50_000, 10, 150, True),
+    (19456, 50_000, 10, 19456, False), (58368, 200_000, 3, 0, False), (19456, 400, 2000, 0, False),
+]
+
+
+@pytest.mark.parametrize("n,k,mean,heavy,lds", RHO)
+def test_rho_form_and_values(n, k, mean, heavy, lds):
+    """The two forms of the products agree with the oracle (the same FP64
+    iteration in another summation order, 1e-10 relative)."""
+    P = synth.make_bernoulli_problem(n, k, mean / n, synth.SQUARED, seed=n + k, support=10)
+    if heavy:
+        rows = np.sort(np.random.default_rng(1).permutation(n)[:heavy])
+        P = _with_column(P, k // 2, rows)
+    _, want, live = O.rho(O.Matrix.of(P), 6)
+    est, names = _rho_kernels(G.Matrix.of(P))
+    assert any("k_rho_spmv" in s for s in names) == lds
+    assert est.k_live == live
+    np.testing.assert_allclose(est.history, want, rtol=1e-10)
+
+
+def test_rho_of_uneven_columns_is_not_slower():
+    """Text-like columns: the longest holds nearly every row.  A group of four
+    lanes walked it alone, 12 times the time of as many entries in even
+    columns."""
+    zipf = synth.c2_zipf_logistic(scale=0.2)
+    even = synth.make_bernoulli_problem(zipf.n, 100_000, zipf.nnz / 1e5 / zipf.n, synth.SQUARED,
+                                        seed=1, support=10)
+    a, b = (_best(lambda: G.estimate_rho(X, 20)) for X in (G.Matrix.of(zipf), G.Matrix.of(even)))
+    assert a <= 4.0 * b, (a, b)
