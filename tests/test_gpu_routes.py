@@ -123,3 +123,12 @@ def test_rho_of_uneven_columns_is_not_slower():
                                         seed=1, support=10)
     a, b = (_best(lambda: G.estimate_rho(X, 20)) for X in (G.Matrix.of(zipf), G.Matrix.of(even)))
     assert a <= 4.0 * b, (a, b)
+
+
+def test_colouring_of_many_cut_columns_is_not_slower():
+    """Columns of about 20 entries are cut into two chunks; every wave stepped
+    through every cut column, six times the time of columns a little shorter."""
+    X = [G.Matrix.of(synth.make_bernoulli_problem(300_000, 30_000, m / 3e5, synth.SQUARED, seed=1,
+                                                  support=10)) for m in (22, 9)]
+    a, b = (_best(lambda: G.color(x)) for x in X)
+    assert a <= 4.0 * b, (a, b)
