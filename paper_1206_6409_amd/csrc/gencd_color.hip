@@ -566,6 +566,13 @@ constexpr int kCgHash = 1024;      // counts a workgroup sums in LDS (2048: 29.3
 constexpr int kCgSG = 16;          // lanes per entry
 constexpr int kCgPer = kWave / kCgSG;  // entries a wave walks at once ...
 constexpr int kCgDeep = 4;         // ... times this many groups of loads in flight
+constexpr int kRowDeep = 4;        // loads in flight along a long row
+constexpr int32_t kLongRow = 512;
+// Mean entries of a row from which on a chunk is one entry per lane group: the
+// rows are the work then, and a frontier of a few columns leaves most waves idle
+// (rows of 200, columns of 50: 381 -> 159 ms; 450 and 300: 225 -> 93 ms).
+constexpr double kCgLongRows = 128.0;
+static_assert((kLongRow - 2 * kCgSG) % kCgSG == 0, "whole steps");
 static_assert(kCgChunk % (kCgPer * kCgDeep) == 0, "whole groups per chunk");
 
 // Control block, at the end of gbits (the bitmaps of cut columns take the
@@ -594,6 +601,7 @@ struct ColorGridArgs {
   int32_t *front_a, *front_b;      // whole columns by round parity
   uint32_t *bits;                  // [kCgCut][kCgWords], all zero between rounds
   ColorCtl *ctl;
+  int32_t chunk;                   // entries of a chunk
 };
 
 __global__ __launch_bounds__(kBlock) void k_color_ents(const int32_t *row_idx, int64_t nnz,
@@ -609,7 +617,7 @@ __global__ __launch_bounds__(kBlock) void k_color_ents(const int32_t *row_idx, i
 // A column whose earlier neighbours all have colours joins a list.
 __device__ __forceinline__ void color_push(const ColorGridArgs &a, int32_t j, int64_t beg,
                                            int32_t len, int32_t *front, int nx, int par) {
-  if (len > kCgChunk) {
+  if (len > a.chunk) {
     const int32_t h = atomicAdd(&a.ctl->cut[nx], 1);
     if (h < kCgCut) {
       agent_store(&a.ctl->cut_beg[par][h], uint32_t(beg));
@@ -661,13 +669,14 @@ __device__ __forceinline__ void color_walk(const ColorGridArgs &a, int64_t e0, i
       x[g] = a.ent[at < e1 ? at : e0];
       if (at >= e1) x[g].z = x[g].x;  // nothing
     }
-    int32_t c[kCgDeep][2], v[kCgDeep][2];
+    int32_t c[kCgDeep][2], v[kCgDeep][2], longest = 0;
 #pragma unroll
     for (int g = 0; g < kCgDeep; ++g)
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int32_t q = x[g].x + u * kCgSG + l;
         c[g][u] = q < x[g].z && q != x[g].y ? a.col_at[q] : -1;
+        longest = max(longest, x[g].z - x[g].x);
       }
 #pragma unroll
     for (int g = 0; g < kCgDeep; ++g)
@@ -685,16 +694,51 @@ __device__ __forceinline__ void color_walk(const ColorGridArgs &a, int64_t e0, i
           atomicOr(&bits[v[g][u] >> 5], 1u << (v[g][u] & 31));
         if (c[g][u] >= 0 && q > x[g].y) later(c[g][u]);
       }
+    // longer rows: the groups' next entries together, and from kLongRow entries
+    // on the whole wave along one row after the other (a group alone, 16 entries
+    // at a time: rows of 200 85 -> 77 ms, a row of 4000 523 -> 208 ms; the whole
+    // wave from 32 entries on: rows of 50 13 -> 22 ms)
+#pragma unroll 1
+    for (int32_t o = 2 * kCgSG + l; o - l < min(longest, kLongRow); o += kCgSG) {
 #pragma unroll
-    for (int g = 0; g < kCgDeep; ++g)  // rows of more than 32 entries
-      for (int32_t q = x[g].x + 2 * kCgSG + l; q < x[g].z; q += kCgSG) {
-        if (q == x[g].y) continue;
-        const int32_t j2 = a.col_at[q];
-        if (q > x[g].y) {
-          later(j2);
-        } else {
-          const int32_t w = agent_load(&a.color[j2]);
-          if (w >= 0 && w < words * 32) atomicOr(&bits[w >> 5], 1u << (w & 31));
+      for (int g = 0; g < kCgDeep; ++g) {
+        const int32_t q = x[g].x + o;
+        c[g][0] = q < x[g].z && q != x[g].y ? a.col_at[q] : -1;
+      }
+#pragma unroll
+      for (int g = 0; g < kCgDeep; ++g)
+        v[g][0] = c[g][0] >= 0 && x[g].x + o < x[g].y ? agent_load(&a.color[c[g][0]]) : -1;
+#pragma unroll
+      for (int g = 0; g < kCgDeep; ++g) {
+        if (v[g][0] >= 0 && v[g][0] < words * 32)
+          atomicOr(&bits[v[g][0] >> 5], 1u << (v[g][0] & 31));
+        if (c[g][0] >= 0 && x[g].x + o > x[g].y) later(c[g][0]);
+      }
+    }
+    if (!__any(longest > kLongRow)) continue;
+#pragma unroll
+    for (int g = 0; g < kCgDeep; ++g)
+#pragma unroll 1
+      for (int s = 0; s < kWave; s += kCgSG) {
+        const int32_t own = __builtin_amdgcn_readlane(x[g].y, s);
+        const int32_t end = __builtin_amdgcn_readlane(x[g].z, s);
+#pragma unroll 1
+        for (int32_t q0 = __builtin_amdgcn_readlane(x[g].x, s) + kLongRow + lane; q0 - lane < end;
+             q0 += kRowDeep * kWave) {
+          int32_t cr[kRowDeep], vr[kRowDeep];
+#pragma unroll
+          for (int u = 0; u < kRowDeep; ++u) {
+            const int32_t q = q0 + u * kWave;
+            cr[u] = q < end && q != own ? a.col_at[q] : -1;
+          }
+#pragma unroll
+          for (int u = 0; u < kRowDeep; ++u)
+            vr[u] = cr[u] >= 0 && q0 + u * kWave < own ? agent_load(&a.color[cr[u]]) : -1;
+#pragma unroll
+          for (int u = 0; u < kRowDeep; ++u) {
+            if (vr[u] >= 0 && vr[u] < words * 32) atomicOr(&bits[vr[u] >> 5], 1u << (vr[u] & 31));
+            if (cr[u] >= 0 && q0 + u * kWave > own) later(cr[u]);
+          }
         }
       }
   }
@@ -792,7 +836,7 @@ __global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
           v = h0 + lane < H ? agent_load(&a.ctl->cut_list[par][h0 + lane]) : 0ull;
           vb = h0 + lane < H ? agent_load(&a.ctl->cut_beg[par][h0 + lane]) : 0u;
         }
-        const int32_t mine = h0 + lane < H ? (int32_t(v >> 32) + kCgChunk - 1) / kCgChunk : 0;
+        const int32_t mine = h0 + lane < H ? (int32_t(v >> 32) + a.chunk - 1) / a.chunk : 0;
         int32_t upto = mine;  // chunks of the columns up to this lane's
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {
@@ -807,8 +851,8 @@ __global__ __launch_bounds__(kCgThreads) void k_color_grid(ColorGridArgs a) {
           const int32_t c = q - (__builtin_amdgcn_readlane(upto, g) - nc);
           for (int32_t u = lane; u < words; u += kWave) bits[u] = 0u;
           const int64_t cb = int64_t(uint32_t(__builtin_amdgcn_readlane(int(vb), g)));
-          const int32_t e1 = (c + 1) * kCgChunk < len ? (c + 1) * kCgChunk : len;
-          color_walk(a, cb + int64_t(c) * kCgChunk, cb + e1, lane, words, bits, hkey, hcnt, next, nx,
+          const int32_t e1 = (c + 1) * a.chunk < len ? (c + 1) * a.chunk : len;
+          color_walk(a, cb + int64_t(c) * a.chunk, cb + e1, lane, words, bits, hkey, hcnt, next, nx,
                      par ^ 1);
           __builtin_amdgcn_wave_barrier();
           uint32_t *const gb = a.bits + int64_t(h0 + g) * kCgWords;
@@ -946,6 +990,7 @@ int color_run(const gencd_csc *X, int32_t *color, int32_t *num_colors, void *ws_
     ga.front_b = w.front_b;
     ga.bits = w.gbits;
     ga.ctl = reinterpret_cast<ColorCtl *>(w.gbits + size_t(kCgCut) * kCgWords);
+    ga.chunk = double(nnz) >= kCgLongRows * double(n) ? kCgPer : kCgChunk;
     hipLaunchKernelGGL(k_color_ents, dim3(g1(nnz)), dim3(kBlock), 0, s, X->row_idx, nnz, w.row_ptr,
                        w.pos_in_row, reinterpret_cast<int4 *>(w.keys_a));
     hipLaunchKernelGGL(k_color_start, dim3(g1(k)), dim3(kBlock), 0, s, ga, w.front_a, w.ctl, w.ctl);

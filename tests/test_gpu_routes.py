@@ -125,6 +125,24 @@ def test_rho_of_uneven_columns_is_not_slower():
     assert a <= 4.0 * b, (a, b)
 
 
+# rows at the edges of a step of 32 and of 16 entries and of the whole wave's
+# share (512), mean rows on both sides of the line for short chunks (128)
+@pytest.mark.parametrize("k,lengths", [
+    (700, [31, 32, 33, 47, 48, 49, 511, 512, 513, 700]),
+    (3000, [32, 33, 511, 512, 513, 767, 768, 769, 3000]),
+    (900, [127, 128, 129, 130]),
+])
+def test_colouring_of_long_rows(k, lengths):
+    rng = np.random.default_rng(k)
+    cols = np.concatenate([np.sort(rng.permutation(k)[:m]) for m in lengths * 4])
+    rows = np.repeat(np.arange(4 * len(lengths)), lengths * 4)
+    n = 4 * len(lengths)
+    col_ptr, row_idx, val = synth.coo_to_csc(n, k, rows, cols, np.ones(rows.size))
+    want, nc, _ = O.color(n, k, col_ptr, row_idx)
+    got, c = G.color(G.Matrix.from_numpy(n, k, col_ptr, row_idx, val))
+    assert c == nc and np.array_equal(got.cpu().numpy(), want)
+
+
 def test_colouring_of_many_cut_columns_is_not_slower():
     """Columns of about 20 entries are cut into two chunks; every wave stepped
     through every cut column, six times the time of columns a little shorter."""
