@@ -667,8 +667,11 @@ __global__ __launch_bounds__(kGridThreads) void k_greedy_grid(IterArgs a, GridCt
 // among 32, 1.2 among 64 and 1.8 among 128 (every member reads every flag);
 // more of them gather and scatter faster.  Per window, 32 / 64 / 128: 2k
 // entries 4.6 / 4.8 / 5.9 us, 8k 6.1 / 6.1 / 7.0, 31k 8.6 / 8.1 / 8.6, 61k
-// 13.0 / 10.0 / 9.9.
-static unsigned grid_size(double nnz) { return nnz <= 8192.0 ? 32 : 64; }
+// 13.0 / 10.0 / 9.9.  More units than the waves of 32 take 64 as well: 2000
+// columns of 3 entries in groups of 32 3.2 -> 2.5 ms (two launches 2.75).
+static unsigned grid_size(double nnz, int64_t units) {
+  return nnz <= 8192.0 && units <= 32 * (kGridThreads / kWave) ? 32 : 64;
+}
 
 template <int GS>
 static void launch_grid_g(const IterArgs &a, int mode, GridCtl *ctl, unsigned long long *bad,
@@ -687,12 +690,13 @@ static void launch_grid_g(const IterArgs &a, int mode, GridCtl *ctl, unsigned lo
 constexpr int64_t kGridMaxWindows = 4096;
 
 int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
-                      unsigned long long *bad, int64_t T, double nnz, int64_t block, hipStream_t s) {
+                      unsigned long long *bad, int64_t T, double nnz, int64_t units,
+                      int64_t block, hipStream_t s) {
   if (mode == 2 && (T > kGreedyMaxT || block < 2 || block > kGreedyMaxBlock))
     return GENCD_ERR_INVALID_ARG;
   if (a.piece > kWave * kUnroll || T < 1 || a.k_live < 1 || a.nrows * 16 > INT32_MAX)
     return GENCD_ERR_INVALID_ARG;
-  const unsigned m = grid_size(nnz);
+  const unsigned m = grid_size(nnz, units);
   for (int64_t t0 = 0; t0 < T; t0 += kGridMaxWindows) {
     if (t0 > 0) {  // the next launch's grid enrols anew
       const int st = fill_i32(reinterpret_cast<int32_t *>(ctl), sizeof(GridCtl) / sizeof(int32_t), 0, s);

@@ -55,11 +55,12 @@ struct GridCtl {
 // All T windows of an epoch whose order is built, in launches of up to 4096
 // windows (mode 0: accept all, 1: Coloring, 2: Thread-Greedy with 2 to
 // kGreedyMaxBlock positions per block and at most kGreedyMaxT windows; pieces of
-// at most 64 * kUnroll entries, rows of at most 2 GiB).  nnz: expected entries of a window.  A grid barrier that
-// runs out sets bit 16 of *bad.
+// at most 64 * kUnroll entries, rows of at most 2 GiB).  nnz, units: expected
+// entries and work units of a window.  A grid barrier that runs out sets bit 16
+// of *bad.
 int launch_epoch_grid(const IterArgs &a, int group, int mode, GridCtl *ctl,
-                      unsigned long long *bad, int64_t T, double nnz, int64_t block,
-                      hipStream_t s);
+                      unsigned long long *bad, int64_t T, double nnz, int64_t units,
+                      int64_t block, hipStream_t s);
 
 // Whole epochs of a small accept-all problem in one workgroup
 // (gencd_solo.hip).

@@ -497,11 +497,30 @@ constexpr int32_t kSoloMaxWindows = 16384;
 // Thread-Greedy replaces three launches, but a wave per block finishes and
 // scatters alone: ahead up to about 40k entries (15k 11.4 against 15.6 us, 56k
 // 18.6 against 18.0).
-constexpr double kGridWindowNnz = 65536.0;
+//
+// A column costs about as much as four entries there (columns of 8, |J| = 6000
+// ahead by 2 to 4%, 8000 with 64k entries behind by as much).  And the line is
+// sharp where a window has more units of work (64 / group columns) than the grid
+// has waves, as each further round is a chain of its own that two launches of
+// many workgroups do not have: columns of 1.7 entries, 1000 units 2.1 -> 2.0 ms,
+// 1250 2.3 -> 2.6, 2500 2.4 -> 3.4; of 3 in groups of 32, 2000 units 2.7 -> 3.4,
+// 10 000 4.2 -> 9.5.  Thread-Greedy is still ahead with 2500 units (3.15 -> 3.07).
+// Unequal windows (colour classes, preset blocks) may have a quarter as many
+// further rounds as windows: the Lasso workload's 557 classes have 34 and gain
+// 1.5 times, 200 classes with 36 in one of them 1.50 -> 1.31 ms an epoch.
+constexpr double kGridWindowNnz = 65536.0, kGridColumnNnz = 4.0, kGridCostNnz = 90112.0;
 constexpr double kGridGreedyNnz = 32768.0;
+constexpr int64_t kGridUnits = 1024, kGridGreedyUnits = 2560;
 bool grid_fits(int64_t nnz, int64_t k_live, int64_t positions, bool greedy) {
-  return double(positions) * double(nnz) / double(k_live) <=
-         (greedy ? kGridGreedyNnz : kGridWindowNnz);
+  const double w = double(positions) * double(nnz) / double(k_live);
+  if (greedy) return w <= kGridGreedyNnz;
+  return w <= kGridWindowNnz && w + kGridColumnNnz * double(positions) <= kGridCostNnz;
+}
+
+// Units of a window, at most eight columns each.
+int64_t grid_units(int64_t positions, int group) {
+  const int64_t per = kWave / std::max(group, 8);
+  return (positions + per - 1) / per;
 }
 
 // Expected long pieces in a window of `positions` columns (sizes the grid;
@@ -683,7 +702,28 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
   if (ran_solo) *ran_solo = solo;
 
   // Mid-size windows: the windows of an epoch in one launch on a grid of
-  // resident workgroups.
+  // resident workgroups.  Rounds of the grid's waves beyond one a window:
+  const auto grid_extra = [&](int64_t T) {
+    const auto extra = [&](int64_t positions) {
+      return std::max<int64_t>(grid_units(positions, su.group) - 1, 0) / kGridUnits;
+    };
+    int64_t sum = 0;
+    if (rule == GENCD_COLORING) {
+      for (int32_t sz : cls_sizes) sum += extra(sz);
+    } else if (rule == GENCD_BLOCK_SHOTGUN) {
+      const int64_t nb = int64_t(su.bp.size());
+      for (int64_t b = 0; b < nb; ++b) {
+        const int64_t kb = block_lo(b + 1, k_live, nb) - block_lo(b, k_live, nb);
+        const int64_t pb = su.bp[size_t(b)];
+        sum += (kb + pb - 1) / pb * extra(pb);
+      }
+    } else if (mode == 2) {
+      sum = grid_units(S, su.group) > kGridGreedyUnits ? T : 0;
+    } else {
+      sum = T * extra(S);
+    }
+    return sum;
+  };
   const auto grid_ok = [&](int64_t positions) {
     const bool accept = mode != 2 || (rule == GENCD_THREAD_GREEDY && p->block >= 2 &&
                                       p->block <= kGreedyMaxBlock &&
@@ -704,7 +744,7 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
                                       prof ? nullptr : gctl, C, S, T, es);
     if (rc) return rc;
     const int64_t mean_pos = T > 0 ? (k_live + T - 1) / T : 0;
-    const bool grid = T > 1 && grid_ok(mean_pos);
+    const bool grid = T > 1 && grid_ok(mean_pos) && grid_extra(T) * 4 <= T;
     if (grid) {
       a.win_off = (rule == GENCD_COLORING || rule == GENCD_BLOCK_SHOTGUN) ? ws.win_off : nullptr;
       a.S = int32_t(S);
@@ -712,7 +752,8 @@ int solve_impl(const gencd_csc *X, const float *y, const gencd_params *p, float 
       a.rs = nullptr;
       rc = launch_epoch_grid(a, su.group, mode, gctl,
                              reinterpret_cast<unsigned long long *>(ws.red) + 10, T,
-                             double(X->nnz) / double(T), p->block, es);
+                             double(X->nnz) / double(T), grid_units(mean_pos, su.group), p->block,
+                             es);
       if (rc) return rc;
     }
     PermKey cpk{};

@@ -67,6 +67,21 @@ def test_tuner_keeps_defaults_that_no_schedule_reaches(tmp_path):
     assert G.autotune(X, y, prm, epochs=3, cache_path=str(old))["from_cache"] == 0
 
 
+@pytest.mark.parametrize("mean,S,group", [(3, 20_000, 8), (3, 5_000, 32), (3, 2_000, 32)])
+def test_many_units_in_a_window(mean, S, group):
+    """Windows of at most 64k entries in more units of work than the resident
+    grid has waves: up to 2.3 times the separate launches' time (a piece of 512
+    keeps those).  The last one's fit the larger of the two grids."""
+    P = synth.make_bernoulli_problem(20_000, 40 * S, mean / 20_000, synth.LOGISTIC, seed=1, support=50)
+    X, y = G.Matrix.of(P), torch.as_tensor(P.y, device="cuda")
+    lam = 0.1 * G.lambda_max(X, y, P.loss)
+    kw = dict(rule="shotgun", select_size=S, seed=3, tol=0.0, max_epochs=16, check_every=16,
+              group=group, residual=1)
+    a, b = (_best(lambda: G.solve(X, y, G.make_params(P.loss, lam, piece=piece, **kw)))
+            for piece in (256, 512))
+    assert a <= 1.2 * b, (a, b)
+
+
 def _rho_kernels(X, iters=6):
     from torch.profiler import ProfilerActivity, profile
     G.estimate_rho(X, 2)
