@@ -191,9 +191,12 @@ __device__ __forceinline__ float row_group_sum(float x) {
   return x;
 }
 
-// Maximum of two doubles that a NaN on either side wins.
+// Maximum of two non-negative doubles that a NaN on either side wins: their
+// order is that of their bits, and a NaN's bits lie above infinity's.
 __device__ __forceinline__ double nan_max(double a, double b) {
-  return a != a || b <= a ? a : b;
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a);
+  const unsigned long long y = (unsigned long long)__double_as_longlong(b);
+  return y > x ? b : a;
 }
 
 // One step of a reduction inside a DPP row: the partner's double, combined.

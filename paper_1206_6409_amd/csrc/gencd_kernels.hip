@@ -2426,8 +2426,41 @@ static void launch_rho_products(const RhoArgs &a, const double *x, double *part,
   hipLaunchKernelGGL(k_rho_cols<G>, dim3(unsigned(a.chunks)), dim3(kRhoThreads), 0, s, a, s64, u);
 }
 
+// Whether a step (two products) is faster with the row vector in LDS than with
+// the check's kernels: both in microseconds, from a fit to 242 matrices
+// (n = 300 to 58 000, 70 k to 30 M entries, columns of 1.5 to 15 000, one column of
+// up to 20 000 among short ones), 5% off on half of them, and the faster form on
+// all but shapes where the two are within 12%.
+//   atomics  47 ns a thousand entries, fewer where a column's rows share cache
+//            lines, and 0.1 us per mean entry of a row (adds to one row queue)
+//   LDS      the partial vectors (stored, and added up) and the slices loaded;
+//            entries per workgroup; a chain per batch of columns of a lane group;
+//            and what a group walks alone past a column's first batch
+// 20 steps, atomics / LDS: 2 M entries in columns of 10 2.4 / 1.4 ms, with one
+// column of 1000 2.4 / 2.2, of 20 000 2.4 / 18.8; 1 M columns in three blocks of
+// 0.6 entries a range 2.5 / 5.1; text-like columns (1 M entries, the longest of
+// 20 000) 1.25 / 17.8; 8000 rows, 140 k entries in columns of 3 0.56 / 0.91, of 22
+// in 1000 rows 0.79 / 0.53; 1000 columns of 2000 in 19 000 rows (9 parts) 1.7 / 2.3.
+static bool rho_lds_pays(const RhoArgs &a, int lanes, int64_t max_len, bool beside) {
+  const double n = double(a.n), N = double(a.nnz), k = double(a.k_live);
+  const double parts = a.parts, chunks = a.chunks, nb = a.nb, groups = kRhoThreads / lanes;
+  const double mean = N / k, density = mean / n, batch = double(lanes) * kUnroll * nb;
+  if (density > 0.4) return false;  // 3.4 / 3.9 ms at 0.55, 1000 columns
+  const double atomics = 0.047e-3 * N / (1.0 + 5.0 * density) + 0.095 * N / n;
+  const double alone = std::max(0.0, double(max_len) - batch) +
+                       (std::ceil(k / parts / groups) - 1.0) * std::max(0.0, mean - batch);
+  const double chains = std::ceil(k / parts / (groups * kRhoCols)) +
+                        nb * std::ceil(k / chunks / std::min(groups * kRhoCols, double(kRhoChunkCols)));
+  const double in_lds = 1.0 + 1e-6 * parts * n + 3e-6 * chunks * n +
+                        0.21e-3 * N * (1.0 / (parts * nb) + 1.0 / chunks) + 0.026e-3 * k +
+                        2.1 * chains + 0.21 * alone / lanes;
+  // beside other rounds the adds cost more than alone: six requests of a server,
+  // one of them 32 / 27 us here and as fast either way alone, 16.8 / 16.2 ms
+  return in_lds <= (beside ? 1.25 : 1.0) * atomics;
+}
+
 int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws &ws, int64_t k_live,
-               int64_t max_len, int iters, hipStream_t s) {
+               int64_t max_len, bool beside, int iters, hipStream_t s) {
   if (!ws.rho_dinv || iters < 1 || iters > kRhoMaxIters || k_live <= 0) return GENCD_ERR_INVALID_ARG;
   const int64_t nk = X->n > X->k ? X->n : X->k;
   unsigned blocks;
@@ -2456,32 +2489,14 @@ int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws 
   parts = std::min<int64_t>(parts, 256 / ra.nb);
   constexpr int64_t kRhoMinParts = 8;
   ra.parts = int32_t(parts);
-  // Entries per range (a column's share of a row block), and the lanes that
-  // take one.  Ranges cost 85 ns a thousand, entries 50 ns a thousand on the
-  // atomics: 1 M columns in two blocks of 1.0 entries a range 20 steps 3.5 ms
-  // (atomics 2.5), of 1.6 3.4 (4.0); in three of 0.6 5.1 (2.5), of 1.1 5.0 (4.0).
+  ra.chunks = int32_t(std::max<int64_t>(1, std::min<int64_t>(X->nnz / 8192, 256)));
+  // entries per range (a column's share of a row block), and the lanes that take one
   const double per = double(X->nnz) / double(k_live) / double(ra.nb);
   const int lanes = per > 96.0 ? 64 : per > 24.0 ? 16 : 4;
-  constexpr double kRhoMinPer = 1.5;
-  // A group of lanes walks its columns alone, about 0.1 us per `lanes` entries,
-  // twice a step.  One column of H entries among 2 M others in columns of 10:
-  // H = 200 1.5 ms, 1000 2.2, 5000 5.8, 20 000 18.8 (atomics 2.4); in columns of
-  // 50, H = 1000 1.7, 5000 2.9, 20 000 7.6 (2.5); of 400, H = 5000 1.8, 20 000 3.3
-  // (2.2); among 20 M in columns of 10, H = 5000 10.3, 20 000 23.9 (20.4).  Text-like
-  // columns (5 M entries, n = 20 000) 17.8 (1.25).
-  const bool even = double(max_len) <= 1e-4 * double(X->nnz) * lanes;
-  // A workgroup of either product takes about 0.6 ns an entry, the atomics
-  // 0.05, less where a column's rows share cache lines.  n = 19 000: 1000 columns
-  // of 2000 entries (9 parts) 2.3 ms (1.7), 3000 (23 parts) 2.3 (5.2); of 15 000
-  // entries, 300 columns (19 parts) 3.8 (1.4), 1000 (65 parts) 3.9 (3.4).
-  const double density = double(X->nnz) / double(k_live) / double(X->n);
-  const bool wide = 0.6 * (1.0 / double(std::max<int64_t>(parts * ra.nb, 1)) + 1.0 / 256.0) <=
-                    0.05 / (1.0 + 5.0 * density);
   const bool lds = ra.nb <= kRhoMaxBlocks && parts >= kRhoMinParts && X->nnz < (int64_t(1) << 30) &&
-                   per >= kRhoMinPer && even && wide;
+                   rho_lds_pays(ra, lanes, max_len, beside);
   hipLaunchKernelGGL(k_rho_init, dim3(grid_for(nk)), dim3(kBlock), 0, s, X->k, X->n, ws.g64,
                      ws.rho_dinv, ws.rho_x, 1.0 / sqrt(double(k_live)), ws.z64, ws.rho_hist, iters);
-  ra.chunks = int32_t(std::max<int64_t>(1, std::min<int64_t>(X->nnz / 8192, 256)));
   ra.bound = reinterpret_cast<int64_t *>(ws.scat);  // counters of the epochs
   static_assert(256 + 1 + 256 + 1 <= kChkRep * 16, "the bounds fit");
   if (lds)

@@ -149,8 +149,9 @@ int launch_fused(const IterArgs &a, int group, int64_t short_bound, int64_t long
 // Power-iteration estimate of the normalised Gram spectral radius; needs the
 // column sums of squares in ws.g64 (left there by launch_curvature) and the
 // rho arrays of the workspace.  Squared norms land in ws.rho_hist[0..iters).
+// beside: other work runs on the device meanwhile.
 int launch_rho(const gencd_csc *X, int32_t n_short, int32_t n_lpieces, const Ws &ws, int64_t k_live,
-               int64_t max_len, int iters, hipStream_t s);
+               int64_t max_len, bool beside, int iters, hipStream_t s);
 // Block Shotgun: preset blocks (base order, block of every column) and the
 // per-block power iteration; needs the column sums of squares in ws.g64.
 // Squared norms land in ws.bhist[t][b].

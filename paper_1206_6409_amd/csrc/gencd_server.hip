@@ -663,6 +663,7 @@ void gencd_server::admission_loop() {
     const size_t ws_bytes = sl.bytes - slot_extra(X->k);
     sl.w_best = reinterpret_cast<float *>(base + ws_bytes);
     sl.su = Setup{};
+    sl.su.beside = true;
     int st = setup(X, sl.req.y, p.loss, &p, base, ws_bytes, (p.flags & GENCD_VALIDATE_DEVICE) != 0,
                    s, &sl.su, wants_rho(&p) ? kRhoIters : 0);
     CheckOut ck{};

@@ -232,7 +232,8 @@ int setup(const gencd_csc *X, const float *y, int loss, const gencd_params *p, v
     // pass left in g64
     out->rho_hist.assign(size_t(rho_iters), 0.0);
     if (out->k_live > 0) {
-      st = launch_rho(X, out->n_short, out->n_lpieces, w, out->k_live, out->max_len, rho_iters, s);
+      st = launch_rho(X, out->n_short, out->n_lpieces, w, out->k_live, out->max_len, out->beside,
+                      rho_iters, s);
       if (st) return st;
       GENCD_HIP(hipMemcpyAsync(out->rho_hist.data(), w.rho_hist, sizeof(double) * size_t(rho_iters),
                                hipMemcpyDeviceToHost, s));

@@ -30,6 +30,7 @@ struct Setup {
   int32_t n_short = 0, n_lpieces = 0;
   int64_t k_live = 0;
   int64_t max_len = 0;           // entries of the longest column (want_max)
+  bool beside = false;           // given: other work runs on the device meanwhile
   std::vector<double> rho_hist;  // spectral-radius estimate after each power iteration
   double rho = 0.0;
   std::vector<double> brho;      // Block Shotgun: rho_b of every preset block

@@ -107,10 +107,11 @@ def _with_column(P, at, rows):
 # group, and what rules the form out: a long column, short ranges, few partial
 # vectors, too many rows
 RHO = [
-    (19456, 50_000, 10, 0, True), (19457, 50_000, 10, 0, True), (38912, 90_000, 12, 0, True),
-    (38913, 90_000, 12, 0, True), (58368, 200_000, 12, 0, True), (58369, 200_000, 12, 0, False),
-    (3000, 6000, 40, 0, True), (3000, 3000, 150, 0, True), (19456, 50_000, 10, 150, True),
-    (19456, 50_000, 10, 19456, False), (58368, 200_000, 3, 0, False), (19456, 400, 2000, 0, False),
+    (19456, 150_000, 10, 0, True), (19457, 150_000, 10, 0, True), (38912, 200_000, 12, 0, True),
+    (38913, 250_000, 12, 0, True), (58368, 250_000, 12, 0, True), (58369, 250_000, 12, 0, False),
+    (3000, 6000, 40, 0, True), (3000, 3000, 150, 0, True), (19456, 150_000, 10, 150, True),
+    (19456, 150_000, 10, 19456, False), (58368, 200_000, 3, 0, False), (19456, 400, 2000, 0, False),
+    (8000, 46_000, 3, 0, False), (1000, 6400, 22, 0, True),
 ]
 
 
