@@ -143,10 +143,12 @@ typedef struct {
                             64..2^22); 0 = library default */
   int32_t group;         /* lanes per short column (4, 8, 16 or 32); columns of
                             at most 4 * group nonzeros are short; 0 = default.
-                            With piece, group and residual all 0 a small problem
-                            may run whole epochs in one launch instead of one
+                            Whole epochs may run in one launch instead of a
                             launch pair per iteration (same iterates up to FP32
-                            rounding); setting one keeps the pairs */
+                            rounding): a small problem in one workgroup, only
+                            with piece, group and residual all 0; mid-size
+                            windows on a resident grid, with any group, a piece
+                            of at most 256 and per-entry residuals */
   int32_t improve_steps; /* "Improve delta_j" (Algorithm 3, section 4.1): up to this
                             many further quadratic-approximation steps on each
                             accepted proposal's 1-D objective, from the state at
@@ -491,7 +493,8 @@ typedef struct {
 } gencd_server_status;
 
 /* arena: device memory owned by the caller for the server's lifetime (the
- * server keeps 4 MiB plus 104 B per slot of it for its work tables);
+ * server keeps gencd_server_overhead_bytes of it, about 4 MiB, for its work
+ * tables);
  * max_slots: concurrent requests (1..256); stream: the rounds run on it and
  * it must stay valid until gencd_server_destroy.  The device current at
  * creation is used by the server's threads.  The server creates one stream

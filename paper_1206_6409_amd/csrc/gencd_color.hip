@@ -551,7 +551,7 @@ __global__ __launch_bounds__(kBlock) void k_round_work(
 // whole column's wave then has its mex, chunks OR their bitmaps into the
 // column's global one, and the last of them (a ticket per column) takes the mex
 // from there.  Colours, lists, counters and bitmaps are agent-scope words; the
-// CSR arrays are only read.  A round is 15 us (whole call 53 -> 28.7 ms): the
+// CSR arrays are only read.  A round is 14 us (whole call 53 -> 26.5 ms): the
 // chain list -> entry -> row -> colours -> LDS counts (5 us), the bitmap's and
 // the ticket's round trips, the counters' atomics, the lists' and the barrier.
 // ---------------------------------------------------------------------------

@@ -1,11 +1,19 @@
 // Host driver of Algorithm 1 and the C-ABI entry points of libgencd.
 //
-// gencd_solve runs, per epoch: the selection order (section 2.1), then for
-// every iteration one Propose launch (Algorithm 2 / 4; for accept-all rules
-// it also applies single-piece updates), the Accept launch of the greedy
-// rules (section 2.3), an Update launch for the remaining updates
-// (Algorithm 3) and a residual refresh.  Every check_every epochs an FP64
-// pass recomputes z = Xw, the objective of Eq. (1) and the KKT violations,
+// gencd_solve runs, per epoch: the selection order (section 2.1), then the
+// iterations in one of three forms, by the size of their windows (solo_plan,
+// grid_fits):
+//   - small windows of accept-all rules: whole epochs, and on small matrices
+//     their checks, in one workgroup (gencd_solo.hip);
+//   - windows of up to some 64k entries: a launch of the resident grid per
+//     epoch (gencd_grid.hip);
+//   - else per iteration one Propose launch (Algorithm 2 / 4; for accept-all
+//     rules it also applies single-piece updates), the Accept launch of the
+//     greedy rules (section 2.3), an Update launch for the remaining updates
+//     (Algorithm 3) and, for large windows, a residual refresh.  Profiling, the
+//     fused and exact-accumulation forms, improve steps, Greedy and Top-Greedy
+//     always take this form.
+// Every check_every epochs an FP64 pass recomputes z = Xw, the objective of Eq. (1) and the KKT violations,
 // re-synchronises the FP32 state from it and decides convergence on the
 // host.
 #include <chrono>

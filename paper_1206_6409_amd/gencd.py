@@ -485,7 +485,8 @@ class Server:
     def info(self):
         """running, waiting, finished_unpolled, arena_used, arena_bytes, rounds
         (Propose/Update launch pairs, or windows of a launch that runs
-        several), slot_rounds (sum of the requests each round advanced) and shared_rounds (rounds advancing two or more)."""
+        several), slot_rounds (sum of the requests each round advanced) and
+        shared_rounds (rounds advancing two or more)."""
         s = ServerStatus()
         _check(lib().gencd_server_info(self._h, C.byref(s)), "gencd_server_info")
         return {f: getattr(s, f) for f, _ in s._fields_}
