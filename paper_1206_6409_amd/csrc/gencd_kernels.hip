@@ -605,10 +605,10 @@ __device__ __forceinline__ void order_pieces(int32_t a, int32_t src, int32_t t0,
 // is written here; the long pieces are laid out by k_order_tail (after
 // k_epoch_order_tiles, which takes the permutation from its table; `part`:
 // pieces of every tile of kOrderTile positions) or by the scan and
-// k_order_desc (after k_epoch_order, for more columns than the table covers).  Bound by the random gather of the
-// records and the walks: 336k live columns 24 us, 28 without the table, 4.5 in
-// index order.  With k_order_tail (8.4 us) two launches instead of seven: 40
-// epochs of Greedy 8.1 -> 7.65 ms.
+// k_order_desc (after k_epoch_order, for more columns than the table covers).
+// Bound by the random gather of the records and the walks: 336k live columns
+// 24 us, 28 without the table, 4.5 in index order.  With k_order_tail (8.4 us)
+// two launches instead of seven: 40 epochs of Greedy 8.1 -> 7.65 ms.
 constexpr int kOrderTile = 1024;
 
 __device__ __forceinline__ int32_t order_put(const int4 *live_rec, int64_t src, int64_t p,
