@@ -16,9 +16,9 @@
 // What bounds it: the dependent instructions of that chain on one wave or a
 // few (about 250 at 5 to 6 cycles each with |J| = 1), not memory.  Measured
 // per window on MI355X, against the two launches it replaces: |J| = 1 of 4
-// entries 0.58 us (7.2 us), |J| = 64 of 4 entries, logistic, 1.25 us (10 us),
+// entries 0.6 us (7.2 us), |J| = 64 of 4 entries, logistic, 1.25 us (10 us),
 // |J| = 96 of 20 entries, squared, 2.4 us (10 us).  Whole solves: n = 400,
-// k = 1000, cyclic, 60 epochs 434 -> 36 ms; Shotgun |J| = 64 to KKT 1e-6
+// k = 1000, cyclic, 60 epochs 434 -> 37 ms; Shotgun |J| = 64 to KKT 1e-6
 // 35 -> 6.2 ms; n = 2000, k = 5000 Lasso, |J| = 96, 3.4 -> 1.4 ms.
 #include <cmath>
 
