@@ -573,6 +573,10 @@ constexpr int32_t kLongRow = 512;
 // (rows of 200, columns of 50: 381 -> 159 ms; 450 and 300: 225 -> 93 ms).
 constexpr double kCgLongRows = 128.0;
 static_assert((kLongRow - 2 * kCgSG) % kCgSG == 0, "whole steps");
+// Entries of a matrix for these walks: a position in the row lists and a step
+// past a row's end stay in 32 bits (more entries take the separate launches).
+constexpr int64_t kCgMaxNnz = INT32_MAX - 1024;
+static_assert(kCgMaxNnz + kLongRow + (kRowDeep + 1) * kWave <= INT32_MAX, "positions in 32 bits");
 static_assert(kCgChunk % (kCgPer * kCgDeep) == 0, "whole groups per chunk");
 
 // Control block, at the end of gbits (the bitmaps of cut columns take the
@@ -979,7 +983,7 @@ int color_run(const gencd_csc *X, int32_t *color, int32_t *num_colors, void *ws_
   int32_t *cur = w.front_a, *nxt = w.front_b;
   int64_t round = 0;
   int32_t ctl_host[8];
-  if (nnz > 0) {
+  if (nnz > 0 && nnz <= kCgMaxNnz) {
     ColorGridArgs ga{};
     ga.col_ptr = X->col_ptr;
     ga.ent = reinterpret_cast<const int4 *>(w.keys_a);  // the four sort buffers, free by now
